@@ -182,10 +182,10 @@ class Workspace {
     T* buf(Slot slot, uint64_t n) {
         return static_cast<T*>(raw(slot, n * sizeof(T)));
     }
-    bool fresh_flags = true;  // flags must be cleared before use
+    uint64_t flags_clear = 0; // leading bytes of the flag buffer known to be clear between queries
     bool in_use = false;      // a query is running on it (a failed one leaves flags unknown)
     uint32_t epoch = 0;               // last epoch handed to an expansion (appending iterations)
-    const void* stamp_seen = nullptr; // stamp buffer those epochs refer to (cleared when it changes)
+    uint64_t stamps_known = 0;        // leading stamps that hold no epoch above it (the rest of the buffer is unset)
 
   private:
     explicit Workspace(hipStream_t s) : s_(s) {}

@@ -167,9 +167,9 @@ Workspace& Workspace::arena(hipStream_t s, NoAlloc& na) {
         w.p_[i] = nullptr;
         w.cap_[i] = 0;
     }
-    w.fresh_flags = true;  // the scratch holds whatever the last call left
+    w.flags_clear = 0;  // the scratch holds whatever the last call left
     w.in_use = false;
-    w.stamp_seen = nullptr;
+    w.stamps_known = 0;
     w.epoch = 0;
     return w;
 }
@@ -200,8 +200,8 @@ void* Workspace::raw(Slot slot, uint64_t bytes) {
         p_[slot] = na_->base + na_->used;
         cap_[slot] = want;
         na_->used += want;
-        if (slot == kFlags) fresh_flags = true;
-        if (slot == kStamp) stamp_seen = nullptr;  // new memory: its stamps are unknown
+        if (slot == kFlags) flags_clear = 0;
+        if (slot == kStamp) stamps_known = 0;
         return p_[slot];
     }
     if (p_[slot]) {
@@ -212,9 +212,8 @@ void* Workspace::raw(Slot slot, uint64_t bytes) {
     const uint64_t want = ((bytes + bytes / 4) + 4095) & ~uint64_t(4095);
     p_[slot] = stream_alloc(want, s_);
     cap_[slot] = want;
-    if (slot == kFlags) fresh_flags = true;
-    // a larger buffer may start at the old one's address: its stamps are unknown all the same
-    if (slot == kStamp) stamp_seen = nullptr;
+    if (slot == kFlags) flags_clear = 0;
+    if (slot == kStamp) stamps_known = 0;
     return p_[slot];
 }
 

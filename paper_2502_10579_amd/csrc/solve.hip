@@ -744,11 +744,12 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
     f.fs1 = ws.buf<uint32_t>(Workspace::kFs1, g.V);
     f.fv1 = ws.buf<uint32_t>(Workspace::kFv1, g.V);
     f.stamp = ws.buf<uint32_t>(Workspace::kStamp, g.V);
-    // stamps below every epoch to come: cleared when the buffer is new (or after a no-allocation
-    // call, whose scratch another call may have used) and before the epoch counter wraps
-    if (f.stamp != ws.stamp_seen || ws.epoch > 0xFFFF0000u) {
+    // stamps below every epoch to come: cleared where the buffer is new, where this graph has more
+    // vertices than any before it on the buffer (a buffer is larger than what was asked for, and the
+    // rest of it is unset), and before the epoch counter wraps
+    if (ws.stamps_known < g.V || ws.epoch > 0xFFFF0000u) {
         fill_u32(f.stamp, g.V, 0u, s);
-        ws.stamp_seen = f.stamp;
+        ws.stamps_known = g.V;
         ws.epoch = 0;
     }
     f.epoch = &ws.epoch;
@@ -761,9 +762,14 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
     f.cnt = reinterpret_cast<FrontierCounters*>(ctl);
     f.stats = reinterpret_cast<unsigned long long*>(ctl + 128);
     f.aux = reinterpret_cast<unsigned long long*>(ctl + 256);
-    // flags are clear after every completed loop; clear them after a failure
-    if (ws.fresh_flags || ws.in_use) fill_u32(reinterpret_cast<uint32_t*>(f.flags), nflag / 4, 0u, s);
-    ws.fresh_flags = false;
+    // flags are clear after every completed loop; clear them after a failure, and where this graph has
+    // more vertices than any before it on the buffer (a stray flag past the last vertex of a graph whose
+    // vertices are no multiple of 8 would be expanded as a vertex)
+    if (ws.in_use) ws.flags_clear = 0;
+    if (ws.flags_clear < nflag) {
+        fill_u32(reinterpret_cast<uint32_t*>(f.flags), nflag / 4, 0u, s);
+        ws.flags_clear = nflag;
+    }
     ws.in_use = true;
     EVQ_LAUNCH("query_init", k_init_frontier, 1, 64, s, f.cnt, f.stats, 8);
     f.p = 0;
