@@ -17,7 +17,7 @@
 #include <algorithm>
 #include <chrono>
 
-#include "evq_internal.h"
+#include "frontier.h"
 
 namespace evq {
 namespace {
@@ -379,12 +379,64 @@ void build_impl(Graph* g, const uint32_t* d_ev, uint64_t N, const uint64_t* d_se
 
 // ------------------------------------------------------------------ ring append
 
-// A[x] = number of rows starting at edge x (x < E); then the source of edge
-// e is (rows starting at or before e) - 1.
-__global__ void k_row_starts(const uint32_t* __restrict__ row_ptr, uint32_t V, uint64_t E, uint32_t* __restrict__ A) {
-    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < V; u += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t x = row_ptr[u];
-        if (x < E) atomicAdd(&A[x], 1u);
+// Sources of consecutive edges.  A block takes a tile of kTileEdges edges,
+// finds the tile's first and last rows with two 64-ary searches over row_ptr
+// and stages the row starts between them in LDS, where each edge's row is a
+// binary search away; a tile that spans more rows than fit (long runs of
+// vertices without edges) searches row_ptr itself between the same two rows.
+constexpr int kTileBlock = 256;
+constexpr uint32_t kTileEdges = 2048;
+constexpr uint32_t kTileRows = 2048;
+struct RowTile {
+    uint32_t lo, hi;
+    uint32_t start[kTileRows];
+};
+
+// Every thread of the block calls it, for the edges [e0, e1) of a graph with edges (e0 < e1).
+__device__ __forceinline__ void row_tile_load(RowTile& t, const uint32_t* __restrict__ row_ptr, uint32_t V,
+                                              uint32_t e0, uint32_t e1) {
+    __syncthreads();  // the tile before is no longer read
+    if (threadIdx.x < 64) {
+        const uint32_t lo = wave_search(row_ptr, V, e0), hi = wave_search(row_ptr, V, e1 - 1);
+        if (threadIdx.x == 0) {
+            t.lo = lo;
+            t.hi = hi;
+        }
+    }
+    __syncthreads();
+    const uint32_t n = t.hi - t.lo + 1;
+    if (n <= kTileRows)
+        for (uint32_t i = threadIdx.x; i < n; i += kTileBlock) t.start[i] = row_ptr[t.lo + i];
+    __syncthreads();
+}
+
+// Row of edge e of the loaded tile: the last row that starts at or before e.
+__device__ __forceinline__ uint32_t row_tile_find(const RowTile& t, const uint32_t* __restrict__ row_ptr, uint32_t e) {
+    uint32_t lo = 0, hi = t.hi - t.lo + 1;
+    if (hi <= kTileRows) {
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (t.start[mid] <= e) lo = mid;
+            else hi = mid;
+        }
+    } else {
+        while (hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if (row_ptr[t.lo + mid] <= e) lo = mid;
+            else hi = mid;
+        }
+    }
+    return t.lo + lo;
+}
+
+// src[e] = row of edge e.
+__global__ void __launch_bounds__(kTileBlock) k_sources(const uint32_t* __restrict__ row_ptr, uint32_t V, uint64_t E,
+                                                        uint32_t* __restrict__ src) {
+    __shared__ RowTile t;
+    for (uint64_t b = (uint64_t)blockIdx.x * kTileEdges; b < E; b += (uint64_t)gridDim.x * kTileEdges) {
+        const uint32_t e0 = (uint32_t)b, e1 = (uint32_t)(b + kTileEdges < E ? b + kTileEdges : E);
+        row_tile_load(t, row_ptr, V, e0, e1);
+        for (uint32_t i = threadIdx.x; i < e1 - e0; i += kTileBlock) src[e0 + i] = row_tile_find(t, row_ptr, e0 + i);
     }
 }
 
@@ -392,14 +444,13 @@ __global__ void k_row_starts(const uint32_t* __restrict__ row_ptr, uint32_t V, u
 // then the batch's deletions (tag 1) and additions (tag 2) with their index.
 // The time field of the key is (tag << ib) | index.
 template <typename KT>
-__global__ void k_encode_append(const uint32_t* __restrict__ A, const uint32_t* __restrict__ S,
-                                const uint32_t* __restrict__ col, const uint32_t* __restrict__ wgt, uint64_t E,
-                                const uint32_t* __restrict__ ev, uint64_t n_del, uint64_t n_ev, int ib, KeyLayout L,
+__global__ void k_encode_append(const uint32_t* __restrict__ src, const uint32_t* __restrict__ col,
+                                const uint32_t* __restrict__ wgt, uint64_t E, const uint32_t* __restrict__ ev, uint64_t n_del, uint64_t n_ev, int ib, KeyLayout L,
                                 KT* __restrict__ keys) {
     const uint64_t n = E + n_ev;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
         if (i < E) {
-            keys[i] = make_key<KT>(S[i] + A[i] - 1u, col[i], wgt[i], i, L);
+            keys[i] = make_key<KT>(src[i], col[i], wgt[i], i, L);
         } else {
             const uint64_t j = i - E;
             const uint64_t tag = j < n_del ? 1u : 2u;
@@ -459,19 +510,14 @@ template <typename KT, int MW>
 void append_impl(const Graph& old, Graph* g, const uint32_t* d_ev, uint64_t n_del, uint64_t n_ev, KeyLayout L, int ib,
                  hipStream_t s, Arena& ar) {
     const uint64_t E = old.E, N = E + n_ev;
-    uint32_t* A = ar.alloc<uint32_t>(E + 1);
-    uint32_t* S = ar.alloc<uint32_t>(E + 1);
-    if (E) {
-        fill_u32(A, E + 1, 0u, s);
-        EVQ_LAUNCH("append_rows", k_row_starts, grid_for(old.V, 256), 256, s, old.row_ptr, old.V, E, A);
-        scan_exclusive(A, S, E, nullptr, s, ar);
-    }
+    uint32_t* src = ar.alloc<uint32_t>(E + 1);
+    if (E)
+        EVQ_LAUNCH("append_sources", k_sources, grid_for(E, kTileEdges), kTileBlock, s, old.row_ptr, old.V, E, src);
     KT* keys = ar.alloc<KT>(N);
     KT* tmp = ar.alloc<KT>(N);
-    EVQ_LAUNCH("append_encode", k_encode_append<KT>, grid_for(N, 256), 256, s, A, S, old.col, old.wgt, E, d_ev, n_del,
+    EVQ_LAUNCH("append_encode", k_encode_append<KT>, grid_for(N, 256), 256, s, src, old.col, old.wgt, E, d_ev, n_del,
                n_ev, ib, L, keys);
-    ar.release(A);
-    ar.release(S);
+    ar.release(src);
     // Only the triple bits are sorted: k_append_masks reads a run's entries in
     // any order (the tag and index in the low bits ride along), and the LSD
     // passes are stable, so the runs come out whole (7 passes instead of 11
@@ -502,15 +548,18 @@ void append_impl(const Graph& old, Graph* g, const uint32_t* d_ev, uint64_t n_de
 // part's stayers + the inserts before it, and each insert at its rank among
 // the part's inserts + the stayers before it.  Every part stays sorted by
 // (dst, w), so the arrays equal those of a full rebuild.
-
-enum : uint8_t { kDrop = 0, kStayFull = 1, kToFull = 2, kToPartial = 3, kStayPartial = 4 };
-
-// src_of holds the exclusive scan of A (rows starting at each edge); the
-// source of edge e is the number of rows starting at or before e, minus one.
-__global__ void k_src_of(const uint32_t* __restrict__ A, uint64_t E, uint32_t* __restrict__ src_of) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < E; e += (uint64_t)gridDim.x * blockDim.x)
-        src_of[e] = src_of[e] + A[e] - 1u;
-}
+//
+// What an edge needs beside its own 8 + 8 MW bytes is one bit per edge (a
+// 64-bit word per 64 edges): whether an event names it and its new bit,
+// whether it stays, whether it moves.  Only the words' stayer counts are
+// scanned; an edge's rank is its word's scanned count plus a population
+// count.  The bound is HBM: the masks once, then every array in and out once.
+//   70M edges, 4M vertices, two-word masks, 20k + 20k updates: 11.7 -> 2.1 ms
+//   a call, placement 0.84 ms for 3.4 GB (4.0 TB/s), classes 0.29 ms for
+//   1.1 GB.  Before, each edge's source came from device atomics on the row
+//   starts (8.5 ms: the vertices without edges share their starts with others,
+//   and same-address atomics serialise) and an E-long scan, the ranks from two
+//   more such scans (0.95 ms in all), and each edge kept a byte of class.
 
 template <typename KT>
 __global__ void k_ev_keys(const uint32_t* __restrict__ ev, uint64_t n_del, uint64_t n_ev, KeyLayout L,
@@ -557,13 +606,14 @@ __device__ __forceinline__ bool mask_bit(const uint64_t* __restrict__ mask, uint
 }
 
 // Each distinct event triple: an edge it names gets its new-snapshot bit
-// (added, or present in the newest snapshot and not deleted) in ovr; an added
-// triple held in no snapshot is new.
+// (added, or present in the newest snapshot and not deleted) in nbit, and its
+// bit in named set; an added triple held in no snapshot is new.
 template <typename KT, int MW>
 __global__ void k_ev_lookup(const KT* __restrict__ utrip, const uint32_t* __restrict__ ufl, uint32_t nu, KeyLayout L,
                             const uint32_t* __restrict__ row_ptr, const uint32_t* __restrict__ row_split,
                             const uint32_t* __restrict__ col, const uint32_t* __restrict__ wgt,
-                            const uint64_t* __restrict__ mask, uint32_t s_prev, uint8_t* __restrict__ ovr,
+                            const uint64_t* __restrict__ mask, uint32_t s_prev,
+                            unsigned long long* __restrict__ named, unsigned long long* __restrict__ nbit,
                             uint32_t* __restrict__ isnew) {
     for (uint64_t k = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; k < nu; k += (uint64_t)gridDim.x * blockDim.x) {
         const KT t = utrip[k];
@@ -579,21 +629,28 @@ __global__ void k_ev_lookup(const KT* __restrict__ utrip, const uint32_t* __rest
         }
         if (e != kNone) {
             const bool nb = add || (mask_bit<MW>(mask, e, s_prev) && !del);
-            ovr[e] = (uint8_t)(2u | (nb ? 1u : 0u));
+            const unsigned long long bit = 1ull << (e & 63);
+            atomicOr(&named[e >> 6], bit);
+            if (nb) atomicOr(&nbit[e >> 6], bit);
         }
         isnew[k] = (e == kNone && add) ? 1u : 0u;
     }
 }
 
+// Edge e's mask with its new-snapshot bit; named, nbit: the words of e's 64 edges.
 template <int MW>
-__device__ __forceinline__ void new_mask(const uint64_t* __restrict__ mask, const uint8_t* __restrict__ ovr,
-                                         uint64_t e, uint32_t s_prev, uint32_t s_new, uint64_t (&m)[MW]) {
+__device__ __forceinline__ void new_mask(const uint64_t (&m0)[MW], uint64_t e, uint64_t named, uint64_t nbit,
+                                         uint32_t s_prev, uint32_t s_new, uint64_t (&m)[MW]) {
+    const uint32_t k = (uint32_t)(e & 63);
+    bool nb = (named >> k) & 1ull ? (nbit >> k) & 1ull : false;
 #pragma unroll
-    for (int q = 0; q < MW; ++q) m[q] = mask[e * MW + q];
-    const uint8_t o = ovr[e];
-    const bool nb = (o & 2u) ? (o & 1u) : ((m[s_prev >> 6] >> (s_prev & 63)) & 1ull);
-    m[s_new >> 6] &= ~(1ull << (s_new & 63));
-    if (nb) m[s_new >> 6] |= 1ull << (s_new & 63);
+    for (int q = 0; q < MW; ++q) {
+        m[q] = m0[q];
+        if (!((named >> k) & 1ull) && q == (int)(s_prev >> 6)) nb = (m0[q] >> (s_prev & 63)) & 1ull;
+    }
+#pragma unroll
+    for (int q = 0; q < MW; ++q)
+        if (q == (int)(s_new >> 6)) m[q] = (m[q] & ~(1ull << (s_new & 63))) | ((uint64_t)nb << (s_new & 63));
 }
 
 template <int MW>
@@ -612,22 +669,74 @@ __device__ __forceinline__ bool mask_any(const uint64_t (&m)[MW]) {
     return any;
 }
 
+enum : uint8_t { kDrop = 0, kStayFull = 1, kToFull = 2, kToPartial = 3, kStayPartial = 4 };
+
 template <int MW>
-__global__ void k_classify(const uint64_t* __restrict__ mask, const uint8_t* __restrict__ ovr, uint64_t E,
-                           uint32_t s_prev, uint32_t s_new, Mask<MW> all, uint8_t* __restrict__ cls,
-                           uint32_t* __restrict__ stay, uint32_t* __restrict__ mover) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < E; e += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t m0[MW], m[MW];
-#pragma unroll
-        for (int q = 0; q < MW; ++q) m0[q] = mask[e * MW + q];
-        new_mask<MW>(mask, ovr, e, s_prev, s_new, m);
-        const bool was = mask_eq<MW>(m0, all), full = mask_eq<MW>(m, all), kept = mask_any<MW>(m);
-        uint8_t c = kDrop;
-        if (kept) c = was ? (full ? kStayFull : kToPartial) : (full ? kToFull : kStayPartial);
-        cls[e] = c;
-        stay[e] = (c == kStayFull || c == kStayPartial) ? 1u : 0u;
-        mover[e] = (c == kToFull || c == kToPartial) ? 1u : 0u;
+__device__ __forceinline__ uint8_t edge_class(const uint64_t (&m0)[MW], const uint64_t (&m)[MW], const Mask<MW>& all) {
+    if (!mask_any<MW>(m)) return kDrop;
+    const bool full = mask_eq<MW>(m, all);
+    return mask_eq<MW>(m0, all) ? (full ? kStayFull : kToPartial) : (full ? kToFull : kStayPartial);
+}
+
+template <int MW>
+__device__ __forceinline__ void load_words(const uint64_t* __restrict__ mask, uint64_t e, uint64_t (&m)[MW]) {
+    if constexpr (MW == 2) {
+        const ulonglong2 x = reinterpret_cast<const ulonglong2*>(mask)[e];  // graph arrays are 256-byte aligned
+        m[0] = x.x;
+        m[1] = x.y;
+    } else {
+        m[0] = mask[e];
     }
+}
+
+// One wave per word of 64 edges, kClassWords words at a time (their masks are
+// all loaded before the first is classed): the word's stayers and movers, its
+// stayer count, and the movers' total.  (E >> 6) + 1 words, so that the word of
+// E itself (the end of the last row) exists.
+constexpr int kClassWords = 4;
+template <int MW>
+__global__ void __launch_bounds__(256) k_classify(const uint64_t* __restrict__ mask, const uint64_t* __restrict__ named,
+                                                  const uint64_t* __restrict__ nbit, uint64_t E, uint32_t s_prev,
+                                                  uint32_t s_new, Mask<MW> all, uint64_t* __restrict__ stay,
+                                                  uint64_t* __restrict__ move, uint32_t* __restrict__ scnt,
+                                                  uint32_t* __restrict__ n_move) {
+    const uint32_t lane = lane_id();
+    const uint64_t nwords = (E >> 6) + 1;
+    const uint64_t nw = (uint64_t)gridDim.x * (256 / 64);
+    uint32_t moved = 0;
+    for (uint64_t w0 = ((blockIdx.x * 256ull + threadIdx.x) >> 6) * kClassWords; w0 < nwords; w0 += nw * kClassWords) {
+        uint64_t m0[kClassWords][MW];
+#pragma unroll
+        for (int k = 0; k < kClassWords; ++k) {
+            const uint64_t e = (w0 + k) * 64 + lane;
+#pragma unroll
+            for (int q = 0; q < MW; ++q) m0[k][q] = 0;
+            if (e < E) load_words<MW>(mask, e, m0[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < kClassWords; ++k) {
+            const uint64_t w = w0 + k, e = w * 64 + lane;
+            if (w >= nwords) break;
+            uint64_t m[MW];
+            new_mask<MW>(m0[k], e, named[w], nbit[w], s_prev, s_new, m);
+            const uint8_t c = e < E ? edge_class<MW>(m0[k], m, all) : kDrop;
+            const uint64_t sb = __ballot(c == kStayFull || c == kStayPartial);
+            const uint64_t mb = __ballot(c == kToFull || c == kToPartial);
+            if (lane == 0) {
+                stay[w] = sb;
+                move[w] = mb;
+                scnt[w] = (uint32_t)__popcll(sb);
+            }
+            moved += (uint32_t)__popcll(mb);
+        }
+    }
+    if (lane == 0 && moved) atomicAdd(n_move, moved);
+}
+
+// Stayers before edge x (x <= E): the scanned count of its word plus those before it in the word.
+__device__ __forceinline__ uint32_t stay_rank(const uint64_t* __restrict__ stay, const uint32_t* __restrict__ spre,
+                                              uint32_t x) {
+    return spre[x >> 6] + (uint32_t)__popcll(stay[x >> 6] & ((1ull << (x & 63)) - 1ull));
 }
 
 // Insert keys (u128): u | part | dst | w | payload (32 bits: a mover's edge id,
@@ -663,13 +772,38 @@ __device__ __forceinline__ InsFields ins_fields(u128 k, InsLayout L) {
     return f;
 }
 
-__global__ void k_ins_movers(const uint8_t* __restrict__ cls, const uint32_t* __restrict__ mpos, uint64_t E,
-                             const uint32_t* __restrict__ src_of, const uint32_t* __restrict__ col,
+// The movers' edge ids, in any order (their keys are sorted next, and their
+// triples are distinct): one thread per word of 64 edges, a wave reserving its
+// movers with one atomic.
+__global__ void __launch_bounds__(256) k_list_movers(const uint64_t* __restrict__ move, uint64_t nwords,
+                                                     uint32_t* __restrict__ n_put, uint32_t* __restrict__ ids) {
+    const uint64_t step = (uint64_t)gridDim.x * 256;
+    for (uint64_t w0 = blockIdx.x * 256ull; w0 < nwords; w0 += step) {
+        const uint64_t w = w0 + threadIdx.x;
+        uint64_t bits = w < nwords ? move[w] : 0ull;
+        const uint32_t c = (uint32_t)__popcll(bits);
+        const uint32_t incl = wave_incl_scan(c), tot = lane_value(incl, 63);
+        if (!tot) continue;
+        uint32_t at = 0;
+        if (lane_id() == 0) at = atomicAdd(n_put, tot);
+        at = lane_value(at, 0) + incl - c;
+        for (; bits; bits &= bits - 1) ids[at++] = (uint32_t)(w * 64) + (uint32_t)__builtin_ctzll(bits);
+    }
+}
+
+// Their insert keys: an edge of the all-present part moves to the partial part and the reverse.
+__global__ void k_ins_movers(const uint32_t* __restrict__ ids, uint32_t nm, const uint32_t* __restrict__ row_ptr,
+                             const uint32_t* __restrict__ row_split, uint32_t V, const uint32_t* __restrict__ col,
                              const uint32_t* __restrict__ wgt, InsLayout L, u128* __restrict__ ikeys) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < E; e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint8_t c = cls[e];
-        if (c != kToFull && c != kToPartial) continue;
-        ikeys[mpos[e]] = ins_key(src_of[e], c == kToFull ? 0u : 1u, col[e], wgt[e], (uint32_t)e, L);
+    for (uint64_t k = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; k < nm; k += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t e = ids[k];
+        uint32_t lo = 0, hi = V;  // the last row that starts at or before e
+        while (hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if (row_ptr[mid] <= e) lo = mid;
+            else hi = mid;
+        }
+        ikeys[k] = ins_key(lo, e < row_split[lo] ? 1u : 0u, col[e], wgt[e], e, L);
     }
 }
 
@@ -708,14 +842,32 @@ __global__ void k_ins_rows(const u128* __restrict__ ikeys, uint32_t ni, InsLayou
     }
 }
 
+// New lengths of each row and of its all-present part.
 __global__ void k_new_rows(const uint32_t* __restrict__ row_ptr, const uint32_t* __restrict__ row_split,
-                           const uint32_t* __restrict__ cS, const uint32_t* __restrict__ icnt, uint32_t V,
-                           uint32_t* __restrict__ len, uint32_t* __restrict__ nf) {
+                           const uint64_t* __restrict__ stay, const uint32_t* __restrict__ spre,
+                           const uint32_t* __restrict__ icnt, uint32_t V, uint32_t* __restrict__ len,
+                           uint32_t* __restrict__ nf) {
     for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < V; u += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t a = row_ptr[u], sp = row_split[u], z = row_ptr[u + 1];
-        const uint32_t f = cS[sp] - cS[a] + icnt[u];
+        const uint32_t ra = stay_rank(stay, spre, a), rs = stay_rank(stay, spre, sp), rz = stay_rank(stay, spre, z);
+        const uint32_t f = rs - ra + icnt[u];
         nf[u] = f;
-        len[u] = f + (cS[z] - cS[sp]) + icnt[(uint64_t)V + u];
+        len[u] = f + (rz - rs) + icnt[(uint64_t)V + u];
+    }
+}
+
+// Per (row, part): the part's new start minus the stayers before its old
+// start, so that a stayer's new position is this plus its rank plus the
+// inserts before it; and the row's new all-present end.
+__global__ void k_shifts(const uint32_t* __restrict__ row_ptr, const uint32_t* __restrict__ row_split,
+                         const uint64_t* __restrict__ stay, const uint32_t* __restrict__ spre,
+                         const uint32_t* __restrict__ rp, const uint32_t* __restrict__ nf, uint32_t V,
+                         uint32_t* __restrict__ shift, uint32_t* __restrict__ new_split) {
+    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < V; u += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t b = rp[u], sp = b + nf[u];
+        new_split[u] = sp;
+        shift[u] = b - stay_rank(stay, spre, row_ptr[u]);
+        shift[(uint64_t)V + u] = sp - stay_rank(stay, spre, row_split[u]);
     }
 }
 
@@ -759,27 +911,48 @@ __device__ __forceinline__ uint32_t ins_before(const u128* __restrict__ ikeys, u
     return lo;
 }
 
+// Every staying edge to its new place: per edge 8 + 8 MW bytes in and out.
 template <int MW>
-__global__ void k_place_stayers(uint64_t E, const uint8_t* __restrict__ cls, const uint32_t* __restrict__ src_of,
-                                const uint32_t* __restrict__ row_ptr, const uint32_t* __restrict__ row_split,
-                                const uint32_t* __restrict__ col, const uint32_t* __restrict__ wgt,
-                                const uint64_t* __restrict__ mask, const uint8_t* __restrict__ ovr, uint32_t s_prev,
-                                uint32_t s_new, const uint32_t* __restrict__ cS, const uint32_t* __restrict__ icnt,
-                                const uint32_t* __restrict__ ioff, const u128* __restrict__ ikeys, InsLayout L,
-                                uint32_t V, NewCsr<MW> o) {
-    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < E; e += (uint64_t)gridDim.x * blockDim.x) {
-        const uint8_t c = cls[e];
-        if (c != kStayFull && c != kStayPartial) continue;
-        const uint32_t u = src_of[e], part = c == kStayPartial ? 1u : 0u;
-        const uint32_t pstart = part ? row_split[u] : row_ptr[u];
-        const uint32_t d = col[e], w = wgt[e];
-        uint32_t pos = o.rp[u] + (part ? o.nf[u] : 0u) + (cS[e] - cS[pstart]);
-        const uint64_t slot = (uint64_t)part * V + u;
-        const uint32_t ic = icnt[slot];
-        if (ic) pos += ins_before(ikeys, ioff[slot], ic, L, d, w);
-        uint64_t m[MW];
-        new_mask<MW>(mask, ovr, e, s_prev, s_new, m);
-        put_edge<MW>(o, u, part, pos, d, w, m);
+__global__ void __launch_bounds__(kTileBlock)
+    k_place_stayers(uint64_t E, const uint32_t* __restrict__ row_ptr, uint32_t V, const uint32_t* __restrict__ col,
+                    const uint32_t* __restrict__ wgt, const uint64_t* __restrict__ mask,
+                    const uint64_t* __restrict__ named, const uint64_t* __restrict__ nbit, uint32_t s_prev,
+                    uint32_t s_new, Mask<MW> all, const uint64_t* __restrict__ stay,
+                    const uint32_t* __restrict__ spre, const uint32_t* __restrict__ shift,
+                    const uint32_t* __restrict__ icnt, const uint32_t* __restrict__ ioff,
+                    const u128* __restrict__ ikeys, InsLayout L, NewCsr<MW> o) {
+    constexpr int kPer = kTileEdges / kTileBlock;
+    __shared__ RowTile t;
+    for (uint64_t b = (uint64_t)blockIdx.x * kTileEdges; b < E; b += (uint64_t)gridDim.x * kTileEdges) {
+        const uint32_t e0 = (uint32_t)b, e1 = (uint32_t)(b + kTileEdges < E ? b + kTileEdges : E);
+        // the tile's edges first: their loads are in flight while its rows are looked up
+        uint32_t d[kPer], w[kPer];
+        uint64_t m0[kPer][MW];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t i = k * kTileBlock + threadIdx.x;
+            const uint32_t x = i < e1 - e0 ? e0 + i : e1 - 1;
+            d[k] = col[x];
+            w[k] = wgt[x];
+            load_words<MW>(mask, x, m0[k]);
+        }
+        row_tile_load(t, row_ptr, V, e0, e1);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const uint32_t i = k * kTileBlock + threadIdx.x, e = e0 + i;
+            if (i >= e1 - e0) break;
+            const uint64_t sw = stay[e >> 6];
+            if (!((sw >> (e & 63)) & 1ull)) continue;
+            uint64_t m[MW];
+            new_mask<MW>(m0[k], e, named[e >> 6], nbit[e >> 6], s_prev, s_new, m);
+            const uint32_t part = mask_eq<MW>(m, all) ? 0u : 1u;  // a stayer's part is that of its new mask
+            const uint32_t u = row_tile_find(t, row_ptr, e);
+            const uint64_t slot = (uint64_t)part * V + u;
+            uint32_t pos = shift[slot] + spre[e >> 6] + (uint32_t)__popcll(sw & ((1ull << (e & 63)) - 1ull));
+            const uint32_t ic = icnt[slot];
+            if (ic) pos += ins_before(ikeys, ioff[slot], ic, L, d[k], w[k]);
+            put_edge<MW>(o, u, part, pos, d[k], w[k], m);
+        }
     }
 }
 
@@ -787,32 +960,29 @@ template <int MW>
 __global__ void k_place_inserts(uint32_t ni, const u128* __restrict__ ikeys, InsLayout L,
                                 const uint32_t* __restrict__ row_ptr, const uint32_t* __restrict__ row_split,
                                 const uint32_t* __restrict__ col, const uint32_t* __restrict__ wgt,
-                                const uint64_t* __restrict__ mask, const uint8_t* __restrict__ ovr, uint32_t s_prev,
-                                uint32_t s_new, const uint32_t* __restrict__ cS, const uint32_t* __restrict__ ioff,
-                                uint32_t V, NewCsr<MW> o) {
+                                const uint64_t* __restrict__ mask, const uint64_t* __restrict__ named,
+                                const uint64_t* __restrict__ nbit, uint32_t s_prev, uint32_t s_new,
+                                const uint64_t* __restrict__ stay, const uint32_t* __restrict__ spre,
+                                const uint32_t* __restrict__ shift, const uint32_t* __restrict__ ioff, uint32_t V,
+                                NewCsr<MW> o) {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < ni; i += (uint64_t)gridDim.x * blockDim.x) {
         const InsFields f = ins_fields(ikeys[i], L);
         const uint32_t a = f.part ? row_split[f.u] : row_ptr[f.u];
         const uint32_t z = f.part ? row_ptr[f.u + 1] : row_split[f.u];
         const uint32_t ps = lower_edge(col, wgt, a, z, f.d, f.w);
-        const uint32_t pos = o.rp[f.u] + (f.part ? o.nf[f.u] : 0u) + (uint32_t)(i - ioff[(uint64_t)f.part * V + f.u]) +
-                             (cS[ps] - cS[a]);
+        const uint64_t slot = (uint64_t)f.part * V + f.u;
+        const uint32_t pos = shift[slot] + stay_rank(stay, spre, ps) + (uint32_t)(i - ioff[slot]);
         uint64_t m[MW];
         if (f.payload >> 31) {
 #pragma unroll
-            for (int q = 0; q < MW; ++q) m[q] = 0;
-            m[s_new >> 6] = 1ull << (s_new & 63);
+            for (int q = 0; q < MW; ++q) m[q] = q == (int)(s_new >> 6) ? 1ull << (s_new & 63) : 0ull;
         } else {
-            new_mask<MW>(mask, ovr, f.payload, s_prev, s_new, m);
+            uint64_t m0[MW];
+            load_words<MW>(mask, f.payload, m0);
+            new_mask<MW>(m0, f.payload, named[f.payload >> 6], nbit[f.payload >> 6], s_prev, s_new, m);
         }
         put_edge<MW>(o, f.u, f.part, pos, f.d, f.w, m);
     }
-}
-
-__global__ void k_new_split(const uint32_t* __restrict__ rp, const uint32_t* __restrict__ nf, uint32_t V,
-                            uint32_t* __restrict__ row_split) {
-    for (uint64_t u = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; u < V; u += (uint64_t)gridDim.x * blockDim.x)
-        row_split[u] = rp[u] + nf[u];
 }
 
 template <typename KT, int MW>
@@ -855,30 +1025,29 @@ void append_incremental(const Graph& old, Graph* g, const uint32_t* d_ev, uint64
     }
 
     // 2. event triples in the held rows; 3. new masks and classes
-    uint8_t* ovr = ar.alloc<uint8_t>(E + 4);
-    fill_u32(reinterpret_cast<uint32_t*>(ovr), (E + 4) / 4, 0u, s);
+    const uint64_t nwords = (E >> 6) + 1;
+    uint64_t* named = ar.alloc<uint64_t>(2 * nwords);
+    uint64_t* nbit = named + nwords;
+    fill_u32(reinterpret_cast<uint32_t*>(named), 4 * nwords, 0u, s);
     uint32_t* isnew = ar.alloc<uint32_t>(nu + 1);
     uint32_t* npos = ar.alloc<uint32_t>(nu + 1);
     if (nu) {
         EVQ_LAUNCH("append_ev_lookup", (k_ev_lookup<KT, MW>), grid_for(nu, 256), 256, s, utrip, ufl, nu, EL,
-                   old.row_ptr, old.row_split, old.col, old.wgt, old.mask, s_prev, ovr, isnew);
+                   old.row_ptr, old.row_split, old.col, old.wgt, old.mask, s_prev, (unsigned long long*)named,
+                   (unsigned long long*)nbit, isnew);
         scan_exclusive(isnew, npos, nu, npos + nu, s, ar);
     } else {
         fill_u32(npos, 1, 0u, s);
     }
-    uint8_t* cls = ar.alloc<uint8_t>(E + 1);
-    uint32_t* cS = ar.alloc<uint32_t>(E + 1);
-    uint32_t* cM = ar.alloc<uint32_t>(E + 1);
-    if (E) {
-        EVQ_LAUNCH("append_classify", k_classify<MW>, grid_for(E, 256), 256, s, old.mask, ovr, E, s_prev, s_new, all,
-                   cls, cS, cM);
-        scan_exclusive(cS, cS, E, cS + E, s, ar);
-        scan_exclusive(cM, cM, E, cM + E, s, ar);
-    } else {
-        fill_u32(cS, 1, 0u, s);
-        fill_u32(cM, 1, 0u, s);
-    }
-    EVQ_HIP(hipMemcpyAsync(mb.h, cM + E, 4, hipMemcpyDeviceToHost, s));
+    uint64_t* stay = ar.alloc<uint64_t>(2 * nwords);
+    uint64_t* move = stay + nwords;
+    uint32_t* spre = ar.alloc<uint32_t>(nwords + 2);
+    uint32_t* n_move = spre + nwords;  // [0] movers, [1] movers listed
+    fill_u32(n_move, 2, 0u, s);
+    EVQ_LAUNCH("append_classify", k_classify<MW>, grid_for(nwords, 4 * kClassWords, 4096), 256, s, old.mask, named, nbit,
+               E, s_prev, s_new, all, stay, move, spre, n_move);
+    scan_exclusive(spre, spre, nwords, nullptr, s, ar);
+    EVQ_HIP(hipMemcpyAsync(mb.h, n_move, 4, hipMemcpyDeviceToHost, s));
     EVQ_HIP(hipMemcpyAsync(mb.h + 1, npos + nu, 4, hipMemcpyDeviceToHost, s));
     EVQ_HIP(hipStreamSynchronize(s));
     const uint32_t nm = mb.h[0], nn = mb.h[1], ni = nm + nn;
@@ -888,17 +1057,12 @@ void append_incremental(const Graph& old, Graph* g, const uint32_t* d_ev, uint64
     uint32_t* icnt = ar.alloc<uint32_t>(2ull * V);
     uint32_t* ioff = ar.alloc<uint32_t>(2ull * V);
     fill_u32(icnt, 2ull * V, 0u, s);
-    uint32_t* src_of = nullptr;
     if (nm) {
-        uint32_t* A = ar.alloc<uint32_t>(E + 1);
-        src_of = ar.alloc<uint32_t>(E + 1);
-        fill_u32(A, E + 1, 0u, s);
-        EVQ_LAUNCH("append_rows", k_row_starts, grid_for(V, 256), 256, s, old.row_ptr, V, E, A);
-        scan_exclusive(A, src_of, E, nullptr, s, ar);
-        EVQ_LAUNCH("append_src", k_src_of, grid_for(E, 256), 256, s, A, E, src_of);
-        ar.release(A);
-        EVQ_LAUNCH("append_ins_movers", k_ins_movers, grid_for(E, 256), 256, s, cls, cM, E, src_of, old.col, old.wgt, IL,
-                   ikeys);
+        uint32_t* ids = ar.alloc<uint32_t>(nm);
+        EVQ_LAUNCH("append_list_movers", k_list_movers, grid_for(nwords, 256, 8192), 256, s, move, nwords, n_move + 1,
+                   ids);
+        EVQ_LAUNCH("append_ins_movers", k_ins_movers, grid_for(nm, 256), 256, s, ids, nm, old.row_ptr, old.row_split, V,
+                   old.col, old.wgt, IL, ikeys);
     }
     if (nn)
         EVQ_LAUNCH("append_ins_new", (k_ins_new<KT, MW>), grid_for(nu, 256), 256, s, utrip, isnew, npos, nu, nm, EL, IL,
@@ -916,8 +1080,8 @@ void append_incremental(const Graph& old, Graph* g, const uint32_t* d_ev, uint64
     o.nf = ar.alloc<uint32_t>((uint64_t)V + 1);
     o.fx = ar.alloc<uint32_t>((uint64_t)V + 1);
     uint32_t* len = ar.alloc<uint32_t>((uint64_t)V + 1);
-    EVQ_LAUNCH("append_rows_new", k_new_rows, grid_for(V, 256), 256, s, old.row_ptr, old.row_split, cS, icnt, V, len,
-               o.nf);
+    EVQ_LAUNCH("append_rows_new", k_new_rows, grid_for(V, 256), 256, s, old.row_ptr, old.row_split, stay, spre, icnt,
+               V, len, o.nf);
     scan_exclusive(len, o.rp, V, o.rp + V, s, ar);
     scan_exclusive(o.nf, o.fx, V, o.fx + V, s, ar);
     EVQ_HIP(hipMemcpyAsync(mb.h, o.rp + V, 4, hipMemcpyDeviceToHost, s));
@@ -937,23 +1101,17 @@ void append_incremental(const Graph& old, Graph* g, const uint32_t* d_ev, uint64
     g->bytes = ((uint64_t)V + 1) * 4 + (uint64_t)V * 4 + E2 * (8 + 8 * MW) + g->n_partial * (12 + 8 * MW);
 
     // 5. placement
-    if (E) {
-        if (!src_of) {
-            uint32_t* A = ar.alloc<uint32_t>(E + 1);
-            src_of = ar.alloc<uint32_t>(E + 1);
-            fill_u32(A, E + 1, 0u, s);
-            EVQ_LAUNCH("append_rows", k_row_starts, grid_for(V, 256), 256, s, old.row_ptr, V, E, A);
-            scan_exclusive(A, src_of, E, nullptr, s, ar);
-            EVQ_LAUNCH("append_src", k_src_of, grid_for(E, 256), 256, s, A, E, src_of);
-            ar.release(A);
-        }
-        EVQ_LAUNCH("append_place", k_place_stayers<MW>, grid_for(E, 256), 256, s, E, cls, src_of, old.row_ptr,
-                   old.row_split, old.col, old.wgt, old.mask, ovr, s_prev, s_new, cS, icnt, ioff, ikeys, IL, V, o);
-    }
+    uint32_t* shift = ar.alloc<uint32_t>(2ull * V);
+    EVQ_LAUNCH("append_shifts", k_shifts, grid_for(V, 256), 256, s, old.row_ptr, old.row_split, stay, spre, o.rp, o.nf,
+               V, shift, g->row_split);
+    if (E)
+        EVQ_LAUNCH("append_place", k_place_stayers<MW>, grid_for(E, kTileEdges), kTileBlock, s, E, old.row_ptr, V,
+                   old.col, old.wgt, old.mask, named, nbit, s_prev, s_new, all, stay, spre, shift, icnt, ioff, ikeys,
+                   IL, o);
     if (ni)
         EVQ_LAUNCH("append_place_ins", k_place_inserts<MW>, grid_for(ni, 256), 256, s, ni, ikeys, IL, old.row_ptr,
-                   old.row_split, old.col, old.wgt, old.mask, ovr, s_prev, s_new, cS, ioff, V, o);
-    EVQ_LAUNCH("append_split", k_new_split, grid_for(V, 256), 256, s, o.rp, o.nf, V, g->row_split);
+                   old.row_split, old.col, old.wgt, old.mask, named, nbit, s_prev, s_new, stay, spre, shift, ioff, V,
+                   o);
     EVQ_HIP(hipStreamSynchronize(s));
 }
 
