@@ -66,7 +66,7 @@ struct LaneGroup {
 // of a union row; the packed reservation counts vertices and tasks.  Union
 // rows of hubs have 10^4-10^5 tasks, so k_btasks writes them (write_tasks).
 __global__ void __launch_bounds__(kCompactBlock) k_bcompact(BatchArgs a, int p, int first) {
-    if (compaction_skips(a.cnt, p, first)) return;
+    if (compaction_skips(a.cnt, p, first ? 1u : a.cnt->status[p])) return;
     compact_flags(
         a.flags, a.V, &a.cnt->packed[p], &a.cnt->far[p], &a.cnt->fmin[p],
         [&](uint32_t v, uint32_t, uint32_t& items, uint32_t& tasks, uint32_t&, uint2&) {
@@ -103,8 +103,8 @@ __device__ __forceinline__ bool lane_has(const uint64_t* __restrict__ mask, uint
 // (up to CH edges of one vertex); lane q relaxes query q over the edges
 // present in its window's intersection (CUP = false) or union (CUP = true).
 template <int A, bool CUP, int MW, int CH>
-__global__ void __launch_bounds__(kBlock) k_bexpand(BatchArgs a, int p, uint32_t* slot) {
-    const unsigned long long cx = expand_prologue(a.cnt, p, slot);
+__global__ void __launch_bounds__(kBlock) k_bexpand(BatchArgs a, int p, unsigned long long* slot) {
+    const unsigned long long cx = expand_prologue(a.cnt, p, p, slot);
     const uint32_t n = edges_of(cx);  // tasks (the items are their vertices)
     if (n == 0) return;
     const uint32_t LQ = a.LQ;
@@ -259,7 +259,7 @@ void batch_loop(BatchArgs a, uint32_t chunk, uint32_t blocks, Frontier& f, hipSt
     const uint32_t cblocks = grid_for(a.V, kCompactIds, 4096);
     const uint32_t tblocks = 2048;
     a.chunk = chunk;
-    auto issue = [&](uint64_t, int p, bool first, uint32_t* slot) {
+    auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         EVQ_LAUNCH("batch_compact", k_bcompact, cblocks, kCompactBlock, s, a, p, first ? 1 : 0);
         EVQ_LAUNCH("batch_tasks", k_btasks, tblocks, 256, s, a, p);
         switch (chunk) {
@@ -313,6 +313,7 @@ void batch_bounds(const Graph& g, uint32_t algo, const Window* wins, const uint3
     while (LQ < nq) LQ <<= 1;
     Workspace& ws = Workspace::get(s);
     Frontier f = make_frontier(g, ws, s);
+    init_frontier(f, s);
     const uint64_t n = (uint64_t)g.V * LQ;
     uint32_t* Xcap = ws.buf<uint32_t>(Workspace::kBatchCap, n + 4);
     uint32_t* Xcup = ws.buf<uint32_t>(Workspace::kBatchCup, n + 4);

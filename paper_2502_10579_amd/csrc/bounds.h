@@ -24,12 +24,16 @@ struct Frontier {
     uint32_t append_edges = 0;   // appending expansions up to this many frontier edges (0: never)
     uint32_t append_items = 0;   // ... or up to this many frontier vertices (0: never)
     FrontierCounters* cnt = nullptr;
+    Team* team = nullptr;        // control block of the teams (frontier.h)
+    uint32_t place = 0;          // which eighth of a grid's blocks forms them
     unsigned long long* stats = nullptr;  // [0] bound-solve edge visits, [1..] relaxer counters
     unsigned long long* aux = nullptr;    // 128 bytes of scratch counters for the reduction
     int p = 0;                            // parity of the next compaction (continues across phases)
     uint32_t delta = 0;                   // near/far step of the bound solves (0: off)
     uint32_t heavy = 0;                   // with delta: gate only vertices with this many edges (0: all)
     uint32_t bdelta = 0;                  // bucket width of the SSSP intersection solve (0: off)
+    bool fresh = true;                    // the counters and statistics have not been initialised yet
+    bool aux_clear = false;               // aux is cleared for the next reduction
     uint64_t items = 0;                   // frontier items processed so far (published counts)
 };
 
@@ -47,7 +51,26 @@ uint32_t choose_bucket_width(uint32_t algo, const Graph& g);
 // not allocate, or all kWeightOrders slots hold other widths).
 const WeightOrder* weight_order_ready(const Graph& g, uint32_t width, hipStream_t s);
 
+// The buffers of one query.  The first intersection solve initialises their
+// counters; a caller that runs none first calls init_frontier.
 Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s);
+void init_frontier(Frontier& f, hipStream_t s);
+
+// Epochs for one launch that may list vertices: the first of kTeamIters, or 0
+// when none are left (it marks flags instead) until a later query clears the
+// stamps.
+inline uint32_t take_epochs(Frontier& f) {
+    if (*f.epoch >= 0xFFFFFFFFu - 2 * kTeamIters) return 0;
+    const uint32_t e = *f.epoch + 1;
+    *f.epoch += kTeamIters;
+    return e;
+}
+
+// Launches kept in flight when teams run the small iterations: a team
+// publishes at its end, usually that the loop is done, and launches issued
+// before that is known cost 9 us; a large iteration publishes at its start and
+// hides the next one's launches.
+constexpr uint64_t kTeamDepth = 1;
 
 // Pull step of the full-window intersection solve: an expansion whose
 // frontier holds at least this share of the all-present edges (fixed point,
@@ -64,8 +87,8 @@ bool reverse_ready(const Graph& g, hipStream_t s);
 uint64_t solve_cap(const Graph& g, uint32_t algo, const Window& W, uint32_t source, uint32_t* R, Frontier& f,
                    hipStream_t s, bool stats);
 
-// R (holding the intersection values) := values on the window's union graph.
-uint64_t solve_cup(const Graph& g, uint32_t algo, const Window& W, uint32_t* R, Frontier& f, hipStream_t s,
-                   bool stats);
+// R := values on the window's union graph, from those on its intersection graph (rcap).
+uint64_t solve_cup(const Graph& g, uint32_t algo, const Window& W, const uint32_t* rcap, uint32_t* R, Frontier& f,
+                   hipStream_t s, bool stats);
 
 }  // namespace evq

@@ -153,13 +153,13 @@ void graph_free(const Graph& g, void* p, hipStream_t s);
 // A call that must not allocate (evq_query_noalloc).  While it is set on a
 // thread, the query path takes its device buffers from `base` by bump
 // allocation (the first kNoAllocSlotBytes hold the frontier loops' published
-// counts, which the host reads back with a copy), reads counters into plain
+// words, which the host reads back with a copy), reads counters into plain
 // host memory, launches untimed and never builds the pull step's reverse CSR.
 struct NoAlloc {
     char* base = nullptr;
     uint64_t cap = 0, used = 0;
 };
-constexpr uint64_t kNoAllocSlotBytes = 256;
+constexpr uint64_t kNoAllocSlotBytes = 512;
 NoAlloc*& noalloc_ctx();  // thread-local; null outside such a call
 // Device address of this device's scratch array (looked up once per device)
 // and its size; throws EVQ_EDEVICE if the lookup fails.
@@ -173,7 +173,7 @@ class Workspace {
   public:
     enum Slot {
         kFlags, kFo, kFd, kFs, kFv, kFo1, kFd1, kFs1, kFv1, kStamp, kControl, kRcap, kRcup, kCidOf, kUlist, kCuo,
-        kRv, kRc, kRuo, kKc, kRecs, kTasks, kX, kBatchCap, kBatchCup, kBatchTable, kUbits, kOrder, kSlots
+        kRv, kRc, kRuo, kRecs, kTasks, kX, kBatchCap, kBatchCup, kBatchTable, kUbits, kOrder, kSlots
     };
     static Workspace& get(hipStream_t s);
     static Workspace& arena(hipStream_t s, NoAlloc& na);
@@ -185,6 +185,7 @@ class Workspace {
     uint64_t flags_clear = 0; // leading bytes of the flag buffer known to be clear between queries
     bool in_use = false;      // a query is running on it (a failed one leaves flags unknown)
     uint32_t epoch = 0;               // last epoch handed to an expansion (appending iterations)
+    uint32_t place = 0;               // which eighth of a grid's blocks forms this workspace's teams
     uint64_t stamps_known = 0;        // leading stamps that hold no epoch above it (the rest of the buffer is unset)
 
   private:

@@ -20,12 +20,21 @@
 // cost one launch.  In a sparse iteration the bound solves' expansion may
 // instead append its improved vertices to the next work list itself (into
 // cnt[p ^ 1], zeroed by the compaction before it); the next compaction then
-// skips its scan.
+// skips its scan.  A run of small iterations is done by one launch (Team,
+// below).
 #pragma once
 
 #include "evq_internal.h"
 
 namespace evq {
+
+// What an expansion publishes for the host, in one 64-bit word: the frontier
+// items it processed (low word), the iterations it ran, and whether the loop
+// is done (nothing was left to process, now or for the next launch).
+constexpr unsigned long long kSlotDone = 1ull << 63;
+__host__ __device__ inline unsigned long long slot_word(uint32_t items, uint32_t iters, bool done) {
+    return (done ? kSlotDone : 0ull) | ((unsigned long long)iters << 32) | items;
+}
 
 struct FrontierCounters {
     unsigned long long packed[2];  // (items << 32) | edges, by parity
@@ -36,7 +45,10 @@ struct FrontierCounters {
     uint32_t heavy;                // with delta > 0: only ids with at least this many edges are gated (0: all)
     uint32_t kall[2];              // smallest order key over the compacted ids with edges, by parity (heavy > 0)
     uint32_t status[2];            // for the compaction of parity q: bit 0 the expansion before it had work
-                                   // or deferred ids, bit 1 it appended the next list itself
+                                   // or deferred ids, bit 1 it appended the next list itself, bit 2 a team
+                                   // left that list (its count is Team::result)
+    uint32_t flip[2];              // the bound solves' item sets at host parity q are those of q ^ flip[q]
+                                   // (a team that ran an even number of iterations moves them)
     // Bucketed schedule with light and heavy edges (bound solves of SSSP):
     uint32_t bdelta;               // bucket width (0: off)
     uint32_t bthr[2];              // the bucket's upper key bound set by the compaction of parity q
@@ -55,18 +67,18 @@ __device__ __forceinline__ void mark(uint8_t* __restrict__ flags, uint32_t v) { 
 // Bytes of the flag array for n ids (a multiple of the 8 ids a lane reads).
 inline uint64_t flag_bytes(uint64_t n) { return (n + 7) & ~uint64_t(7); }
 
-// Expansion prologue: read this iteration's counts, tell the next compaction
-// whether there was work and whether this expansion appends the next list
-// itself (`appends`, the same on every block), publish the item count to the
-// host slot.
+// Expansion prologue: read this iteration's counts (of item parity p), tell the
+// next compaction (host parity h ^ 1) whether there was work and whether this
+// expansion appends the next list itself (`appends`, the same on every block),
+// publish the item count to the host slot.
 // When nothing was near but ids were deferred, the threshold moves to the
 // smallest deferred order key plus delta, so the next compaction releases the
 // best of them.  When only heavy ids are gated, the threshold also follows the
 // frontier: it rises to the smallest key of this iteration's ids plus delta,
 // so a heavy id is expanded once its value is within delta of the best one
 // still moving (and, with positive steps, close to final).
-__device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* c, int p, uint32_t* slot,
-                                                              bool appends = false) {
+__device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* c, int h, int p,
+                                                              unsigned long long* slot, bool appends = false) {
     const unsigned long long x = c->packed[p];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         const uint32_t f = c->far[p];
@@ -77,41 +89,179 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
             t = u > t ? u : t;
         }
         c->thr = t > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)t;
-        c->status[p ^ 1] = (x != 0ull || f ? 1u : 0u) | (appends ? 2u : 0u);
+        c->status[h ^ 1] = (x != 0ull || f ? 1u : 0u) | (appends ? 2u : 0u);
+        c->flip[h ^ 1] = (uint32_t)(h ^ p);
         // the other parity's deferral counters, last read by the compaction
         // before this expansion, start afresh for the next compaction
         c->far[p ^ 1] = 0u;
         c->fmin[p ^ 1] = 0xFFFFFFFFu;
         c->kall[p ^ 1] = 0xFFFFFFFFu;
-        __hip_atomic_store(slot, items_of(x) + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        const uint32_t n = items_of(x) + f;
+        __hip_atomic_store(slot, slot_word(n, n ? 1u : 0u, n == 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     return x;
 }
 
-// Compaction prologue: zero the other parity's item counters (the previous
-// iteration's, read only by kernels that have finished) for the next
-// iteration, clear this parity's bucket reports for the expansion that
-// follows, and say whether the scan can be skipped: the previous expansion
-// had no work and deferred nothing (no flag can be set), or it appended the
-// next list itself.  The first compaction of a loop always scans.
-__device__ __forceinline__ bool compaction_skips(FrontierCounters* c, int p, int first) {
+// A team: up to kTeamBlocks blocks of one expansion launch that run a loop's
+// small iterations themselves, with a barrier of their own between iterations
+// instead of a kernel boundary.
+//
+// What bounds a small iteration is latency: two launches of 2.4 us each and
+// their start and drain (10-12 us an iteration as launches, whatever its
+// size), against 1.3-1.7 us for a barrier over blocks that share an L2 and
+// about 2 us for the chain of dependent accesses of an expansion.
+//
+// Members are the candidate blocks (every eighth block of the grid, which the
+// dispatcher places on one XCD) that are running when the first of them, after
+// a short wait, closes the registration; so every member is resident and the
+// barrier cannot wait for a block that has yet to start.  Blocks that come
+// later find the registration closed and leave.  Nothing depends on where the
+// members run: all they share goes through agent-scope relaxed atomic loads,
+// stores and read-modify-writes, and a member's accesses have completed
+// (s_waitcnt) before it arrives at the barrier.  An agent-scope fence would do
+// as well but writes the L2 back (7.6 us a barrier against 1.3).
+struct Team {
+    uint32_t reg;     // members registered; bit 31: closed
+    uint32_t n;       // their number, once closed
+    uint32_t err;     // a wait ran out
+    uint32_t ran;     // tag of the last launch that a team ran
+    uint32_t pad0[28];
+    uint32_t arrive;  // barrier arrivals so far
+    uint32_t pad1[31];
+    uint32_t gen;     // barriers completed
+    uint32_t pad2[31];
+    // (items << 32) | edges of the lists: iteration k reads [k % 3], appends into
+    // [(k + 1) % 3] and clears [(k + 2) % 3], which iteration k - 1 read
+    unsigned long long packed[3];
+    unsigned long long result;  // count of the list the team left
+};
+constexpr uint32_t kTeamBlocks = 64;
+constexpr uint32_t kTeamIters = 1024;      // most iterations of one launch
+constexpr uint32_t kTeamSpins = 1u << 24;  // bound of every wait (seconds); past it the launch gives up
+constexpr uint64_t kTeamBytes = 1024;      // control bytes of a team
+static_assert(sizeof(Team) <= kTeamBytes, "team control block");
+
+__device__ __forceinline__ void team_reset(Team* t) {  // one thread, in a launch before the team's
+    t->reg = t->n = t->err = t->arrive = t->gen = 0u;
+    t->packed[0] = t->packed[1] = t->packed[2] = 0ull;
+}
+
+template <typename T>
+__device__ __forceinline__ T shared_load(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void shared_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// End of a team's launch at host parity h, by one thread: after k iterations the
+// current list has count x and item parity q; `items` were processed.  What the
+// next launches read is written to places that this launch's late blocks do
+// not look at, or whose change only tells them to leave.  `tag` (never 0)
+// tells the rest of this iteration's launches that a team has run it.
+__device__ __forceinline__ void team_leave(FrontierCounters* c, Team* t, uint32_t tag, int h, int q,
+                                           unsigned long long x, uint32_t items, uint32_t k, unsigned long long* slot) {
+    t->result = x;
+    t->ran = tag;
+    c->status[h ^ 1] = x ? 5u : 4u;
+    c->flip[h ^ 1] = (uint32_t)(q ^ h ^ 1);
+    __hip_atomic_store(slot, slot_word(items, k, x == 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+struct TeamRun {
+    uint32_t rank, n, gen;
+};
+
+// Every thread of a block calls it; true for the members' blocks.  `lane8`
+// picks which eighth of the grid's blocks are the candidates.
+__device__ __forceinline__ bool team_join(Team* t, uint32_t lane8, TeamRun& r) {
+    const uint32_t eighths = gridDim.x < 8u ? gridDim.x : 8u;
+    if (blockIdx.x % 8u != lane8 % eighths || blockIdx.x / 8u >= kTeamBlocks) return false;
+    __shared__ uint32_t s_rank, s_n;
+    if (threadIdx.x == 0) {
+        uint32_t rank = kNone, n = 0;
+        const uint32_t k = shared_load(&t->reg) >> 31 ? 1u << 31 : atomicAdd(&t->reg, 1u);
+        if (!(k >> 31)) {
+            rank = k;
+            const uint32_t want = (gridDim.x - lane8 % eighths + 7u) / 8u;
+            const uint32_t all = want < kTeamBlocks ? want : kTeamBlocks;
+            if (k == 0) {
+                for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < all; ++i) __builtin_amdgcn_s_sleep(1);
+                n = atomicOr(&t->reg, 1u << 31);
+                shared_store(&t->n, n);
+            } else {
+                for (uint32_t i = 0; i < kTeamSpins && n == 0; ++i) n = shared_load(&t->n);
+                if (n == 0) rank = kNone;
+            }
+        }
+        s_rank = rank;
+        s_n = n;
+    }
+    __syncthreads();
+    r.rank = s_rank;
+    r.n = s_n;
+    r.gen = 0;
+    return r.rank != kNone;
+}
+
+// Barrier over the team; every thread of every member calls it.  False: a
+// member did not arrive in time (the caller leaves without publishing, which
+// the host reports as an error).
+__device__ __forceinline__ bool team_barrier(Team* t, TeamRun& r) {
+    __shared__ uint32_t s_ok;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's loads, stores and atomics have completed
+    __syncthreads();
+    ++r.gen;
+    if (threadIdx.x == 0) {
+        uint32_t ok = 1;
+        if (__hip_atomic_fetch_add(&t->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == r.n * r.gen) {
+            shared_store(&t->gen, r.gen);
+        } else {
+            uint32_t i = 0;
+            while (shared_load(&t->gen) < r.gen)
+                if (++i >= kTeamSpins || shared_load(&t->err)) {
+                    shared_store(&t->err, 1u);
+                    ok = 0;
+                    break;
+                }
+        }
+        s_ok = ok;
+    }
+    __syncthreads();
+    return s_ok != 0;
+}
+
+// Compaction prologue (host parity h, item parity p, status st of this
+// iteration): zero the other item parity's counters (the previous iteration's,
+// read only by kernels that have finished) for the next iteration, clear this
+// parity's bucket reports for the expansion that follows, and say whether the
+// scan can be skipped: the previous expansion had no work and deferred nothing
+// (no flag can be set), it appended the next list itself, or a team left one
+// (its count is put in place here).  The first compaction of a loop scans,
+// unless its list is there already.
+__device__ __forceinline__ bool compaction_skips(FrontierCounters* c, int p, uint32_t st, Team* team = nullptr) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->packed[p ^ 1] = 0ull;
+        if (team && (st & 4u)) c->packed[p] = team->result;
         c->near[p] = 0u;
         c->nmin[p] = 0xFFFFFFFFu;
     }
-    return !first && c->status[p] != 1u;
+    return st != 1u;
 }
 
 // Largest i in [0, n) with off[i] <= x (off ascending, off[0] == 0), found by
 // the whole wave with a 64-ary search.  Every lane must call it.
-__device__ __forceinline__ uint32_t wave_search(const uint32_t* __restrict__ off, uint32_t n, uint32_t x) {
+// SHARED: off is written by other blocks of this launch (a team's list).
+template <bool SHARED = false>
+__device__ __forceinline__ uint32_t wave_search(const uint32_t* off, uint32_t n, uint32_t x) {
+    auto at = [&](uint32_t i) { return SHARED ? shared_load(off + i) : off[i]; };
     uint32_t lo = 0, hi = n;  // answer in [lo, hi)
     const uint32_t lane = lane_id();
     while (hi - lo > 64) {
         const uint32_t step = (hi - lo + 63) / 64;
         const uint32_t idx = lo + lane * step;
-        const bool ok = idx < hi && off[idx] <= x;
+        const bool ok = idx < hi && at(idx) <= x;
         const uint64_t b = __ballot(ok);
         const uint32_t last = 63u - (uint32_t)__clzll((unsigned long long)b);  // lane 0 is always ok
         const uint32_t nlo = lo + last * step;
@@ -120,7 +270,7 @@ __device__ __forceinline__ uint32_t wave_search(const uint32_t* __restrict__ off
         hi = nhi;
     }
     const uint32_t idx = lo + lane;
-    const bool ok = idx < hi && off[idx] <= x;
+    const bool ok = idx < hi && at(idx) <= x;
     const uint64_t b = __ballot(ok);
     return lo + 63u - (uint32_t)__clzll((unsigned long long)b);
 }
@@ -348,10 +498,12 @@ __device__ __forceinline__ void task_list_flush(TaskList& tl, uint64_t* __restri
 class HostSlots {
   public:
     static constexpr uint32_t kSlots = 256;
-    static constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+    static constexpr uint32_t kMail = kSlots;  // three words of mail from one kernel: arrived, then two counts
+    static constexpr uint32_t kWords = kSlots + 8;
+    static constexpr unsigned long long kEmpty = ~0ull;  // no published word (slot_word never gives it)
     static HostSlots& get();  // one per host thread
-    uint32_t* host() const { return h_; }
-    uint32_t* dev() const { return d_; }
+    unsigned long long* host() const { return h_; }
+    unsigned long long* dev() const { return d_; }
     // Slot numbering runs on across loops, so that the iterations a finished
     // loop issued past its end (still queued) never write a slot that the
     // next loop has just reset.
@@ -359,60 +511,68 @@ class HostSlots {
 
   private:
     HostSlots();
-    uint32_t* h_ = nullptr;
-    uint32_t* d_ = nullptr;
+    unsigned long long* h_ = nullptr;
+    unsigned long long* d_ = nullptr;
 };
 
-// Issues iterations (issue(it, parity, first)) `depth` ahead of the one whose
-// published count it waits for; stops at the first iteration with count 0.
-// Returns the number of non-empty iterations and adds the published counts
-// (items processed) to *items; f_parity is advanced past every issued
-// iteration.
+// Issues launches of an iteration (issue(it, parity, first)) `depth` ahead of
+// the one whose published word it waits for; stops at the first that says the
+// loop is done.  Returns the number of non-empty iterations and adds the
+// published counts (items processed) to *items; f_parity is advanced past
+// every issued launch.
 template <typename IssueFn>
 uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_iters, const char* what,
-                    uint64_t* items = nullptr);
+                    uint64_t* items = nullptr, uint64_t depth = 0);
 
-void wait_slot(volatile uint32_t* slot, hipStream_t s, const char* what);
+void wait_slot(volatile unsigned long long* slot, hipStream_t s, const char* what);
 
 // Iterations kept in flight by drive_loop: EVQ_LAUNCH_DEPTH (1..32), default 3.
 uint64_t launch_depth();
 // EVQ_TRACE_LOOPS=1: drive_loop prints each iteration's published count to stderr.
 bool trace_loops();
 
-// Inside a no-allocation call: the published counts go to the first words of
-// the scratch array; each batch of launch_depth() + 1 iterations is followed
+// Counts a published word in; true when it says the loop is done.
+inline bool loop_step(unsigned long long w, const char* what, uint64_t max_iters, uint64_t& consumed, uint64_t* items) {
+    const uint32_t n = (uint32_t)w, it = (uint32_t)(w >> 32) & 0x7FFFFFFFu;
+    if (trace_loops())
+        fprintf(stderr, "[evq] %s iteration %llu: %u (%u iterations)\n", what, (unsigned long long)consumed, n, it);
+    if (items) *items += n;
+    consumed += it;
+    if (consumed > max_iters) fail(EVQ_ENOCONV, std::string(what) + " exceeded its iteration cap");
+    return (w & kSlotDone) != 0;
+}
+
+// Inside a no-allocation call: the published words go to the first bytes of
+// the scratch array; each batch of depth + 1 launches is followed
 // by one copy of its counts to host memory and a stream synchronisation.
 template <typename IssueFn>
 uint64_t drive_loop_sync(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_iters, const char* what,
-                         uint64_t* items, NoAlloc& na) {
-    static_assert(kNoAllocSlotBytes >= 33 * 4, "slots of one batch");
-    uint32_t* dslots = reinterpret_cast<uint32_t*>(na.base);
-    const uint64_t batch = launch_depth() + 1;
-    uint32_t h[33];
+                         uint64_t* items, uint64_t depth, NoAlloc& na) {
+    static_assert(kNoAllocSlotBytes >= 33 * 8, "slots of one batch");
+    unsigned long long* dslots = reinterpret_cast<unsigned long long*>(na.base);
+    const uint64_t batch = (depth ? depth : launch_depth()) + 1;
+    unsigned long long h[33];
     uint64_t issued = 0, consumed = 0;
     for (;;) {
         for (uint64_t j = 0; j < batch; ++j, ++issued) {
             issue(issued, f_parity, issued == 0, dslots + j);
             f_parity ^= 1;
         }
-        EVQ_HIP(hipMemcpyAsync(h, dslots, batch * 4, hipMemcpyDeviceToHost, s));
+        EVQ_HIP(hipMemcpyAsync(h, dslots, batch * 8, hipMemcpyDeviceToHost, s));
         EVQ_HIP(hipStreamSynchronize(s));
         for (uint64_t j = 0; j < batch; ++j) {
-            if (trace_loops()) fprintf(stderr, "[evq] %s iteration %llu: %u\n", what, (unsigned long long)consumed, h[j]);
-            if (h[j] == 0) return consumed;
-            if (items) *items += h[j];
-            if (++consumed > max_iters) fail(EVQ_ENOCONV, std::string(what) + " exceeded its iteration cap");
+            if (loop_step(h[j], what, max_iters, consumed, items)) return consumed;
         }
     }
 }
 
 template <typename IssueFn>
 uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_iters, const char* what,
-                    uint64_t* items) {
-    if (NoAlloc* na = noalloc_ctx()) return drive_loop_sync(issue, f_parity, s, max_iters, what, items, *na);
-    const uint64_t kDepth = launch_depth();
+                    uint64_t* items, uint64_t depth) {
+    if (NoAlloc* na = noalloc_ctx()) return drive_loop_sync(issue, f_parity, s, max_iters, what, items, depth, *na);
+    const uint64_t kDepth = depth ? depth : launch_depth();
     HostSlots& hs = HostSlots::get();
-    uint64_t issued = 0, consumed = 0;
+    uint64_t issued = 0, taken = 0, consumed = 0;
     const uint64_t base = hs.next;
     struct Advance {
         HostSlots& hs;
@@ -422,7 +582,7 @@ uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_it
     uint64_t end = base;
     Advance adv{hs, end};
     for (;;) {
-        while (issued < consumed + kDepth) {
+        while (issued < taken + kDepth) {
             const uint32_t k = (uint32_t)((base + issued) % HostSlots::kSlots);
             __atomic_store_n(&hs.host()[k], HostSlots::kEmpty, __ATOMIC_RELEASE);
             issue(issued, f_parity, issued == 0, hs.dev() + k);
@@ -430,12 +590,10 @@ uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_it
             ++issued;
             end = base + issued;
         }
-        volatile uint32_t* slot = hs.host() + ((base + consumed) % HostSlots::kSlots);
+        volatile unsigned long long* slot = hs.host() + ((base + taken) % HostSlots::kSlots);
         wait_slot(slot, s, what);
-        if (trace_loops()) fprintf(stderr, "[evq] %s iteration %llu: %u\n", what, (unsigned long long)consumed, *slot);
-        if (*slot == 0) break;
-        if (items) *items += *slot;
-        if (++consumed > max_iters) fail(EVQ_ENOCONV, std::string(what) + " exceeded its iteration cap");
+        ++taken;
+        if (loop_step(*slot, what, max_iters, consumed, items)) break;
     }
     return consumed;
 }

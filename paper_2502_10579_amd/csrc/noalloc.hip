@@ -14,7 +14,7 @@ namespace evq {
 
 namespace {
 
-constexpr uint64_t kScratchBytes = 128ull << 20;  // 128 MiB per GPU
+constexpr uint64_t kScratchBytes = (128ull << 20) + 4096;  // 128 MiB per GPU, and the control blocks
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kScratchBytes];

@@ -127,6 +127,7 @@ __device__ __forceinline__ void block_scan3(const uint32_t (&v)[3], uint32_t (&p
 struct UCounters {
     unsigned long long ids;
     unsigned long long rows;  // (rows << 32) | edges
+    unsigned long long done;  // blocks that have added theirs
 };
 
 // U = {v : R_cap[v] != R_cup[v]} (all vertices when rcap is null).  Every U
@@ -154,8 +155,15 @@ __global__ void __launch_bounds__(kUBlock) k_unstable(const uint32_t* __restrict
                                                       uint32_t* __restrict__ cid_of, uint32_t* __restrict__ ulist,
                                                       uint32_t* __restrict__ cuo, uint32_t* __restrict__ rv,
                                                       uint32_t* __restrict__ rc, uint32_t* __restrict__ ruo,
-                                                      uint8_t* __restrict__ ubits, UCounters* cnt) {
+                                                      uint32_t* __restrict__ kc, uint8_t* __restrict__ ubits,
+                                                      UCounters* cnt, FrontierCounters* fc,
+                                                      unsigned long long* mail) {
     __shared__ unsigned long long base_id, base_row;
+    // the relaxation's first compaction adds to these; a bound solve that a team finished leaves its last list's count
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        fc->packed[0] = fc->packed[1] = 0ull;
+        fc->flip[0] = fc->flip[1] = 0u;
+    }
     // 16-byte accesses need aligned bound arrays (the caller's, for evq_query_bounds); cid_of is a workspace buffer
     const bool al = rcap && (((uintptr_t)rcap | (uintptr_t)rcup) % 16 == 0) && (uintptr_t)cid_of % 16 == 0;
     for (uint64_t b0 = (uint64_t)blockIdx.x * kUPerBlock; b0 < V; b0 += (uint64_t)gridDim.x * kUPerBlock) {
@@ -201,6 +209,7 @@ __global__ void __launch_bounds__(kUBlock) k_unstable(const uint32_t* __restrict
                 cids[k] = id;
                 ulist[id] = (uint32_t)v;
                 cuo[id] = edge;
+                kc[id] = 0u;
                 if (deg[k]) {
                     rv[row] = (uint32_t)v;
                     rc[row] = id;
@@ -220,6 +229,14 @@ __global__ void __launch_bounds__(kUBlock) k_unstable(const uint32_t* __restrict
                 if (v0 + k < V) cid_of[v0 + k] = cids[k];
         }
         __syncthreads();
+    }
+    // the last block to add its counts mails the totals to the host (its own
+    // atomics have returned, so they are in)
+    if (mail && threadIdx.x == 0 && atomicAdd(&cnt->done, 1ull) + 1 == gridDim.x) {
+        __hip_atomic_store(mail + 1, shared_load(&cnt->ids), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(mail + 2, shared_load(&cnt->rows), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __threadfence_system();
+        __hip_atomic_store(mail, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -338,7 +355,11 @@ struct RelaxArgs {
     // compact id; then each task as (chunk << 32 | compact id).
     uint32_t* fo;
     uint32_t* fv;
-    uint64_t* tasks;
+    uint64_t* tasks[2];  // by item parity
+    // A team's lists (k_relax_team): stamps over compact ids, its control block
+    uint32_t* stamp;
+    Team* team;
+    uint32_t place;
     FrontierCounters* cnt;
     unsigned long long* stats;  // [1] edge visits, [2] lane relaxations, [3] seed edges
     uint32_t nU;
@@ -366,8 +387,11 @@ __device__ __forceinline__ void add_stat(unsigned long long* p, uint32_t v) {
 // subgraph is small; with a large one the block that holds a hub would write
 // most of an iteration's tasks alone, so k_relax_tasks writes them instead.
 template <bool DIRECT>
-__global__ void __launch_bounds__(kCompactBlock) k_relax_compact(RelaxArgs r, int p, int first) {
-    if (compaction_skips(r.cnt, p, first)) return;
+__global__ void __launch_bounds__(kCompactBlock) k_relax_compact(RelaxArgs r, int h, int first) {
+    const int p = h ^ (int)uniform(r.cnt->flip[h]);
+    uint64_t* const tasks_out = r.tasks[p];
+    if (blockIdx.x == 0 && threadIdx.x == 0) team_reset(r.team);  // for k_relax_team
+    if (compaction_skips(r.cnt, p, first ? 1u : r.cnt->status[h], r.team)) return;
     __shared__ TaskList tl;
     if (DIRECT) task_list_init(tl);
     compact_flags(
@@ -382,20 +406,22 @@ __global__ void __launch_bounds__(kCompactBlock) k_relax_compact(RelaxArgs r, in
                 r.fo[item] = task;
                 r.fv[item] = c;
             } else if (tasks == 1) {
-                r.tasks[task] = c;
+                tasks_out[task] = c;
             } else {
-                task_list_add(tl, r.tasks, c, task, tasks);
+                task_list_add(tl, tasks_out, c, task, tasks);
             }
         },
         nullptr, [&]() {
-            if (DIRECT) task_list_flush(tl, r.tasks);
+            if (DIRECT) task_list_flush(tl, tasks_out);
         });
 }
 
-// Frontier items of parity p -> the iteration's tasks (write_tasks).
-__global__ void __launch_bounds__(kBlock) k_relax_tasks(RelaxArgs r, int p) {
+// Frontier items of this iteration -> its tasks (write_tasks), unless a team left them.
+__global__ void __launch_bounds__(kBlock) k_relax_tasks(RelaxArgs r, int h, int first) {
+    if (!first && (r.cnt->status[h] & 4u)) return;
+    const int p = h ^ (int)uniform(r.cnt->flip[h]);
     const unsigned long long cx = r.cnt->packed[p];
-    write_tasks(r.fo, r.fv, items_of(cx), edges_of(cx), r.tasks);
+    write_tasks(r.fo, r.fv, items_of(cx), edges_of(cx), r.tasks[p]);
 }
 
 // Seeding pass (the parfor over the reduced addition batches in Algorithm 2):
@@ -503,10 +529,13 @@ __global__ void __launch_bounds__(kBlock) k_relax_seed(RelaxArgs r, const uint32
 // since no store of the kernel can reach them.
 template <int A, int LG, bool ST>
 __global__ void __launch_bounds__(kBlock)
-    k_relax(RelaxArgs r, const uint64_t* __restrict__ tasks, const uint32_t* __restrict__ cuo,
-            const uint32_t* __restrict__ kc, const void* __restrict__ recs_v, int p, uint32_t* slot) {
+    k_relax(RelaxArgs r, const uint64_t* __restrict__ tasks0, const uint64_t* __restrict__ tasks1,
+            const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc, const void* __restrict__ recs_v, int h,
+            unsigned long long* slot) {
     using T = Lanes<LG>;
-    const unsigned long long cx = expand_prologue(r.cnt, p, slot);
+    const int p = h ^ (int)uniform(r.cnt->flip[h]);
+    const uint64_t* __restrict__ tasks = p ? tasks1 : tasks0;
+    const unsigned long long cx = expand_prologue(r.cnt, h, p, slot);
     const uint32_t n = edges_of(cx);  // tasks (the items are their vertices)
     if (n == 0) return;
     const Rec<T::NLW>* __restrict__ recs = static_cast<const Rec<T::NLW>*>(recs_v);
@@ -587,15 +616,19 @@ __global__ void __launch_bounds__(kBlock)
 // values laid out snapshot-minor).
 template <int A, int LG, int kStagePerWave, bool ST>
 __global__ void __launch_bounds__(kBlock)
-    k_relax_staged(RelaxArgs r, const uint64_t* __restrict__ tasks, const uint32_t* __restrict__ cuo,
-                   const uint32_t* __restrict__ kc, const void* __restrict__ recs_v, int p, uint32_t* slot) {
+    k_relax_staged(RelaxArgs r, const uint64_t* __restrict__ tasks0, const uint64_t* __restrict__ tasks1,
+                   const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc, const void* __restrict__ recs_v,
+                   int h, uint32_t tag, unsigned long long* slot) {
     using T = Lanes<LG>;
     constexpr int kGroups = (kBlock / 64) * T::G;             // lane groups per block
     constexpr int kStageTasks = kGroups * kStagePerWave;      // tasks per round
     constexpr int kStageRecs = kStageTasks * (int)kRelaxChunk;
     __shared__ uint32_t s_c[kStageTasks], s_e0[kStageTasks], s_ne[kStageTasks];
     __shared__ Rec<T::NLW> s_rec[kStageTasks][kRelaxChunk];
-    const unsigned long long cx = expand_prologue(r.cnt, p, slot);
+    if (tag && r.team->ran == tag) return;  // a team ran this iteration and published
+    const int p = h ^ (int)uniform(r.cnt->flip[h]);
+    const uint64_t* __restrict__ tasks = p ? tasks1 : tasks0;
+    const unsigned long long cx = expand_prologue(r.cnt, h, p, slot);
     const uint32_t n = edges_of(cx);  // tasks
     if (n == 0) return;
     const Rec<T::NLW>* __restrict__ recs = static_cast<const Rec<T::NLW>*>(recs_v);
@@ -678,6 +711,174 @@ __global__ void __launch_bounds__(kBlock)
         }
         __syncthreads();  // the staged tasks are read until here
     }
+}
+
+// Small iterations by a team (frontier.h), in a launch of their own before the
+// relaxation's: list q of tasks with (vertices << 32) | tasks = x into list
+// q ^ 1.  A member stages its tasks and relaxes them as k_relax_staged does,
+// with values read past the L1; the first lane group to improve a destination
+// in this iteration (its stamp moves to the iteration's epoch) lists it, and
+// the block writes the tasks of all it listed behind one reservation.
+// As three launches an iteration over a few tasks takes 15-19 us.
+template <int A, int LG, bool ST>
+__device__ __forceinline__ void team_relax(const RelaxArgs& r, const uint32_t* __restrict__ cuo,
+                                           const uint32_t* __restrict__ kc, const void* __restrict__ recs_v,
+                                           const TeamRun& team, int q, unsigned long long x, unsigned long long* count,
+                                           uint32_t epoch) {
+    using T = Lanes<LG>;
+    constexpr int kPer = 2;                                      // tasks per lane group and round
+    constexpr uint32_t kGroups = (kBlock / 64) * T::G;           // lane groups per block
+    constexpr uint32_t kStageTasks = kGroups * kPer;             // tasks per round
+    constexpr uint32_t kStageRecs = kStageTasks * kRelaxChunk;   // and their edges: the most vertices a round lists
+    constexpr uint32_t kScan = (kStageRecs + kBlock - 1) / kBlock;
+    __shared__ uint32_t s_c[kStageTasks], s_e0[kStageTasks], s_ne[kStageTasks];
+    __shared__ Rec<T::NLW> s_rec[kStageTasks][kRelaxChunk];
+    __shared__ uint32_t s_id[kStageRecs], s_nt[kStageRecs], s_pre[kStageRecs], s_w[kBlock / 64], s_n, s_base;
+    const Rec<T::NLW>* __restrict__ recs = static_cast<const Rec<T::NLW>*>(recs_v);
+    const uint64_t* tasks = r.tasks[q];
+    uint64_t* next = r.tasks[q ^ 1];
+    const uint32_t n = edges_of(x);
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    const int g = LG >= 64 ? 0 : (int)lane / LG;
+    const int i0 = LG >= 64 ? (int)lane : (int)lane % LG;
+    const uint32_t grp = wave * T::G + g;
+    for (uint32_t t0 = team.rank * kStageTasks; t0 < n; t0 += team.n * kStageTasks) {
+        if (threadIdx.x == 0) s_n = 0;
+        for (uint32_t j = threadIdx.x; j < kStageTasks; j += kBlock) {
+            uint32_t c = 0, e0 = 0, ne = 0;
+            if (t0 + j < n) {
+                const uint64_t tk = shared_load(tasks + t0 + j);
+                c = (uint32_t)tk;
+                const uint32_t rb = cuo[c], re = rb + kc[c];
+                e0 = rb + (uint32_t)(tk >> 32) * kRelaxChunk;
+                ne = re - e0 < kRelaxChunk ? re - e0 : kRelaxChunk;
+            }
+            s_c[j] = c;
+            s_e0[j] = e0;
+            s_ne[j] = ne;
+        }
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < kStageRecs; j += kBlock) {
+            const uint32_t tt = j / kRelaxChunk, k = j % kRelaxChunk;
+            Rec<T::NLW> rc;
+            rc.dst = 0;
+            rc.w = 0;
+#pragma unroll
+            for (int m = 0; m < T::NLW; ++m) rc.lanes[m] = 0;
+            if (k < s_ne[tt]) rc = recs[s_e0[tt] + k];
+            s_rec[tt][k] = rc;
+        }
+        __syncthreads();
+        uint32_t lanes_done = 0, edges_done = 0;
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const uint32_t tt = grp * kPer + m;
+            const uint32_t ne = s_ne[tt];
+            uint32_t xu[T::SPL], cur[kRelaxChunk][T::SPL];
+#pragma unroll
+            for (int s = 0; s < T::SPL; ++s)
+                xu[s] = ne ? shared_load(&r.X[(uint64_t)s_c[tt] * T::S + i0 + 64 * s]) : Alg<A>::unreached;
+#pragma unroll
+            for (uint32_t k = 0; k < kRelaxChunk; ++k)
+#pragma unroll
+                for (int s = 0; s < T::SPL; ++s) {
+                    const int i = i0 + 64 * s;
+                    const bool bit = (s_rec[tt][k].lanes[s] >> (i & 63)) & 1ull;
+                    cur[k][s] = bit ? shared_load(&r.X[(uint64_t)s_rec[tt][k].dst * T::S + i]) : Alg<A>::unreached;
+                }
+            edges_done += ne;
+#pragma unroll
+            for (uint32_t k = 0; k < kRelaxChunk; ++k) {
+                const Rec<T::NLW> rc = s_rec[tt][k];
+                bool imp = false;
+#pragma unroll
+                for (int s = 0; s < T::SPL; ++s) {
+                    const int i = i0 + 64 * s;
+                    if ((rc.lanes[s] >> (i & 63)) & 1ull) {
+                        ++lanes_done;
+                        const uint32_t cand = Alg<A>::extend(xu[s], rc.w);
+                        if (Alg<A>::better(cand, cur[k][s])) {
+                            Alg<A>::improve_nr(&r.X[(uint64_t)rc.dst * T::S + i], cand);
+                            imp = true;
+                        }
+                    }
+                }
+                if (group_any<LG>(imp) && i0 == 0 && atomicMax(&r.stamp[rc.dst], epoch) != epoch) {
+                    const uint32_t nt = (kc[rc.dst] + kRelaxChunk - 1) / kRelaxChunk;
+                    if (nt) {
+                        const uint32_t at = atomicAdd(&s_n, 1u);
+                        s_id[at] = rc.dst;
+                        s_nt[at] = nt;
+                    }
+                }
+            }
+        }
+        if (ST) {
+            add_stat<true>(&r.stats[1], i0 == 0 ? edges_done : 0u);
+            add_stat<true>(&r.stats[2], lanes_done);
+        }
+        __syncthreads();
+        const uint32_t na = s_n;
+        if (na) {  // the same on every thread
+            uint32_t nt[kScan], sum = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < kScan; ++k) {
+                const uint32_t j = threadIdx.x * kScan + k;
+                nt[k] = j < na ? s_nt[j] : 0u;
+                sum += nt[k];
+            }
+            const uint32_t incl = wave_incl_scan(sum);
+            if (lane == 63) s_w[wave] = incl;
+            __syncthreads();
+            uint32_t pre = incl - sum, tot = 0;
+            for (uint32_t w = 0; w < kBlock / 64; ++w) {
+                pre += w < wave ? s_w[w] : 0u;
+                tot += s_w[w];
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kScan; ++k) {
+                const uint32_t j = threadIdx.x * kScan + k;
+                if (j < na) s_pre[j] = pre;
+                pre += nt[k];
+            }
+            if (threadIdx.x == 0) s_base = edges_of(atomicAdd(count, ((unsigned long long)na << 32) | tot));
+            __syncthreads();
+            for (uint32_t t = threadIdx.x; t < tot; t += kBlock) {
+                uint32_t lo = 0, hi = na;  // the last entry whose tasks start at or before t
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (s_pre[mid] <= t) lo = mid;
+                    else hi = mid;
+                }
+                shared_store(next + s_base + t, ((uint64_t)(t - s_pre[lo]) << 32) | s_id[lo]);
+            }
+        }
+        __syncthreads();  // what the round staged is read until here
+    }
+}
+
+template <int A, int LG, bool ST>
+__global__ void __launch_bounds__(kBlock)
+    k_relax_team(RelaxArgs r, const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc,
+                 const void* __restrict__ recs, int h, uint32_t limit, uint32_t epoch, unsigned long long* slot) {
+    const int p = h ^ (int)uniform(r.cnt->flip[h]);
+    unsigned long long x = r.cnt->packed[p];
+    if (items_of(x) == 0 || edges_of(x) > limit || epoch == 0) return;
+    TeamRun team;
+    if (!team_join(r.team, r.place, team)) return;
+    uint32_t k = 0, items = 0;
+    int q = p;
+    for (;;) {
+        team_relax<A, LG, ST>(r, cuo, kc, recs, team, q, x, &r.team->packed[(k + 1) % 3], epoch + k);
+        if (team.rank == 0 && threadIdx.x == 0) shared_store(&r.team->packed[(k + 2) % 3], 0ull);
+        items += items_of(x);
+        ++k;
+        q ^= 1;
+        if (!team_barrier(r.team, team)) return;
+        x = shared_load(&r.team->packed[k % 3]);
+        if (x == 0 || edges_of(x) > limit || k == kTeamIters) break;
+    }
+    if (team.rank == 0 && threadIdx.x == 0) team_leave(r.cnt, r.team, epoch, h, q, x, items, k, slot);
 }
 
 // ------------------------------------------------------------------ init / K5
@@ -1031,7 +1232,7 @@ void reduce_edges(const Graph& g, Reduced& r, const Window& W, uint32_t NLW, Wor
 // Builds U's compact ids and the reduced subgraph.  all_vertices: U = V.
 // One host read-back (|U|, rows, edges) sizes the subgraph buffer.
 Reduced reduce_graph(const Graph& g, const uint32_t* rcap, const uint32_t* rcup, bool all_vertices, const Window& W,
-                     uint32_t NLW, const Frontier& f, Workspace& ws, Mailbox& mb, hipStream_t s,
+                     uint32_t NLW, Frontier& f, Workspace& ws, Mailbox& mb, hipStream_t s,
                      uint32_t split_above = 0xFFFFFFFFu) {
     Reduced r;
     const uint32_t V = g.V;
@@ -1042,13 +1243,26 @@ Reduced reduce_graph(const Graph& g, const uint32_t* rcap, const uint32_t* rcup,
     uint32_t* rv = r.rv = ws.buf<uint32_t>(Workspace::kRv, V);
     uint32_t* rc = r.rc = ws.buf<uint32_t>(Workspace::kRc, V);
     uint32_t* ruo = r.ruo = ws.buf<uint32_t>(Workspace::kRuo, V);
+    r.kc = f.fd1;  // V entries of the bound solves' item sets, free from here on
     UCounters* uc = reinterpret_cast<UCounters*>(f.aux);
-    fill_u32(reinterpret_cast<uint32_t*>(uc), sizeof(UCounters) / 4, 0u, s);
+    if (!f.aux_clear) fill_u32(reinterpret_cast<uint32_t*>(uc), sizeof(UCounters) / 4, 0u, s);
+    f.aux_clear = false;
+    // the counts come back through mapped host memory (a copy and a stream synchronisation took 15 us more)
+    HostSlots* hs = noalloc_ctx() ? nullptr : &HostSlots::get();
+    if (hs) __atomic_store_n(&hs->host()[HostSlots::kMail], HostSlots::kEmpty, __ATOMIC_RELEASE);
     EVQ_LAUNCH("compact_unstable", k_unstable, grid_for(V, kUPerBlock, 65535), kUBlock, s,
-               all_vertices ? nullptr : rcap, rcup, V, g.row_ptr, r.cid_of, r.ulist, r.cuo, rv, rc, ruo, r.ubits, uc);
-    EVQ_HIP(hipMemcpyAsync(mb.h, uc, sizeof(UCounters), hipMemcpyDeviceToHost, s));
-    EVQ_HIP(hipStreamSynchronize(s));
-    const unsigned long long* hc = reinterpret_cast<const unsigned long long*>(mb.h);
+               all_vertices ? nullptr : rcap, rcup, V, g.row_ptr, r.cid_of, r.ulist, r.cuo, rv, rc, ruo, r.kc, r.ubits,
+               uc, f.cnt, hs ? hs->dev() + HostSlots::kMail : nullptr);
+    unsigned long long hc[2];
+    if (hs) {
+        wait_slot(hs->host() + HostSlots::kMail, s, "unstable set");
+        hc[0] = hs->host()[HostSlots::kMail + 1];
+        hc[1] = hs->host()[HostSlots::kMail + 2];
+    } else {
+        EVQ_HIP(hipMemcpyAsync(mb.h, uc, sizeof(hc), hipMemcpyDeviceToHost, s));
+        EVQ_HIP(hipStreamSynchronize(s));
+        std::memcpy(hc, mb.h, sizeof(hc));
+    }
     r.nU = (uint32_t)hc[0];
     r.nR = (uint32_t)(hc[1] >> 32);
     r.TU = (uint32_t)hc[1];
@@ -1057,15 +1271,13 @@ Reduced reduce_graph(const Graph& g, const uint32_t* rcap, const uint32_t* rcup,
         r.split = true;
         return r;
     }
-    reduce_edges(g, r, W, NLW, ws, s);
+    reduce_edges(g, r, W, NLW, ws, s);  // kc starts at zero (k_unstable)
     return r;
 }
 
 // The reduced subgraph's records for window W over the unstable set of r
-// (rebuilt in place: kc and the records).
+// (kc must start at zero).
 void reduce_edges(const Graph& g, Reduced& r, const Window& W, uint32_t NLW, Workspace& ws, hipStream_t s) {
-    r.kc = ws.buf<uint32_t>(Workspace::kKc, r.nU);
-    fill_u32(r.kc, r.nU, 0u, s);
     r.recs = ws.raw(Workspace::kRecs, (r.TU + 1) * (NLW == 1 ? sizeof(Rec<1>) : sizeof(Rec<2>)));
     if (r.TU) {
         ReduceArgs a;
@@ -1113,7 +1325,15 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     ra.flags = f.flags;
     ra.fo = f.fo;  // V entries each, free once the bound solves are done (nU <= V)
     ra.fv = f.fv;
-    ra.tasks = ws.buf<uint64_t>(Workspace::kTasks, (uint64_t)red.nU + red.TU / kRelaxChunk + 64);
+    const uint64_t max_tasks = (uint64_t)red.nU + red.TU / kRelaxChunk + 64;
+    // a team lists tasks into a second buffer; a no-allocation call whose scratch holds one only does without
+    const NoAlloc* na = noalloc_ctx();
+    const bool two = !na || na->used + 2 * max_tasks * 8 + 256 <= na->cap;
+    ra.tasks[0] = ws.buf<uint64_t>(Workspace::kTasks, (two ? 2 : 1) * max_tasks);
+    ra.tasks[1] = two ? ra.tasks[0] + max_tasks : ra.tasks[0];
+    ra.stamp = f.stamp;
+    ra.team = f.team;
+    ra.place = f.place;
     ra.cnt = f.cnt;
     ra.stats = f.stats;
     ra.nU = red.nU;
@@ -1146,23 +1366,33 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     const uint32_t staged = LG >= 8 ? tuning().relax_staged : 0u;
     const uint32_t sblocks = grid_for((uint64_t)red.nU + red.TU / kRelaxChunk,
                                       (kBlock / 64) * T::G * (staged ? staged : 1), EVQ_RELAX_BLOCKS);
-    auto issue = [&](uint64_t, int p, bool first, uint32_t* slot) {
+    // iterations of at most one round of a team (2 tasks per lane group and member) go to it
+    const uint32_t team_tasks = staged && two ? kTeamBlocks * (kBlock / 64) * T::G * 2 : 0u;
+    auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         if (direct) {
             EVQ_LAUNCH("relax_compact", k_relax_compact<true>, cblocks, kCompactBlock, s, ra, p, first ? 1 : 0);
         } else {
             EVQ_LAUNCH("relax_compact", k_relax_compact<false>, cblocks, kCompactBlock, s, ra, p, first ? 1 : 0);
-            EVQ_LAUNCH("relax_tasks", k_relax_tasks, tblocks, kBlock, s, ra, p);
+            EVQ_LAUNCH("relax_tasks", k_relax_tasks, tblocks, kBlock, s, ra, p, first ? 1 : 0);
+        }
+        uint32_t epoch = 0;
+        if (team_tasks) {
+            epoch = take_epochs(f);
+            EVQ_LAUNCH("relax_team", (k_relax_team<A, (LG >= 8 ? LG : 8), ST>), 8 * kTeamBlocks, kBlock, s, ra, ra.cuo,
+                       ra.kc, ra.recs, p, team_tasks, epoch, slot);
         }
         if (staged == 2)
-            EVQ_LAUNCH("relax", (k_relax_staged<A, (LG >= 8 ? LG : 8), 2, ST>), sblocks, kBlock, s, ra, ra.tasks,
-                       ra.cuo, ra.kc, ra.recs, p, slot);
+            EVQ_LAUNCH("relax", (k_relax_staged<A, (LG >= 8 ? LG : 8), 2, ST>), sblocks, kBlock, s, ra,
+                       ra.tasks[0], ra.tasks[1], ra.cuo, ra.kc, ra.recs, p, epoch, slot);
         else if (staged == 4)
-            EVQ_LAUNCH("relax", (k_relax_staged<A, (LG >= 8 ? LG : 8), 4, ST>), sblocks, kBlock, s, ra, ra.tasks,
-                       ra.cuo, ra.kc, ra.recs, p, slot);
+            EVQ_LAUNCH("relax", (k_relax_staged<A, (LG >= 8 ? LG : 8), 4, ST>), sblocks, kBlock, s, ra,
+                       ra.tasks[0], ra.tasks[1], ra.cuo, ra.kc, ra.recs, p, epoch, slot);
         else
-            EVQ_LAUNCH("relax", (k_relax<A, LG, ST>), rblocks, kBlock, s, ra, ra.tasks, ra.cuo, ra.kc, ra.recs, p, slot);
+            EVQ_LAUNCH("relax", (k_relax<A, LG, ST>), rblocks, kBlock, s, ra, ra.tasks[0], ra.tasks[1], ra.cuo, ra.kc,
+                       ra.recs, p, slot);
     };
-    qo.st.iters_relax = drive_loop(issue, f.p, s, (uint64_t)g.V + 2, "snapshot relaxation");
+    qo.st.iters_relax = drive_loop(issue, f.p, s, (uint64_t)g.V + 2, "snapshot relaxation", nullptr,
+                                   team_tasks ? kTeamDepth : 0);
 }
 
 template <int A>
@@ -1254,13 +1484,12 @@ void bounds_impl(const Graph& g, uint32_t algo, uint32_t source, const Window& W
     const bool st = qo.want_stats;
     qo.st.iters_cap = solve_cap(g, algo, W, source, rcap, f, s, st);
     tm.mark();
-    EVQ_LAUNCH("copy_bound", k_copy4, grid_for((g.V + 3) / 4, 256 * 4, 8192), 256, s, rcap, rcup, g.V);
     if (st) {
         qo.st.edges_cap = read_stat(f.stats, 0, s);
         qo.st.updates_cap = read_stat(f.stats, 4, s);
     }
     qo.st.items_cap = f.items;
-    qo.st.iters_cup = solve_cup(g, algo, W, rcup, f, s, st);
+    qo.st.iters_cup = solve_cup(g, algo, W, rcap, rcup, f, s, st);
     tm.mark();
     qo.st.items_cup = f.items - qo.st.items_cap;
     if (st) {
@@ -1456,6 +1685,7 @@ void run_tail_compact(const Graph& g, uint32_t algo, uint32_t source, const Wind
     Timer tm(st, s);
     tm.mark();
     Frontier f = make_frontier(g, ws, s);
+    init_frontier(f, s);
     tail_impl(g, algo, source, W, c.rcap, rcup, f, ws, nullptr, &c, qo, s, tm);
     ws.in_use = false;
     if (st) {
@@ -1509,7 +1739,10 @@ void run_sequential(const Graph& g, uint32_t algo, uint32_t source, const Window
         Wi.w[Wi.b >> 6] = 1ull << (Wi.b & 63);
         Wi.full = g.K == 1;
         if (i == 0) red = reduce_graph(g, rcap, rcup, false, Wi, 1, f, ws, mb, s);
-        else if (red.nU) reduce_edges(g, red, Wi, 1, ws, s);
+        else if (red.nU) {
+            fill_u32(red.kc, red.nU, 0u, s);
+            reduce_edges(g, red, Wi, 1, ws, s);
+        }
         uint32_t* X = nullptr;
         if (red.nU) {
             X = ws.buf<uint32_t>(Workspace::kX, red.nU);
@@ -1555,6 +1788,7 @@ void run_plain(const Graph& g, uint32_t algo, uint32_t source, const Window& W, 
     Timer tm(st, s);
     tm.mark();
     Frontier f = make_frontier(g, ws, s);
+    init_frontier(f, s);
     const uint32_t LG = pick_lg(W.L);
     const uint32_t NLW = LG > 64 ? 2 : 1;
     Reduced red = reduce_graph(g, nullptr, nullptr, true, W, NLW, f, ws, mb, s);

@@ -2,6 +2,7 @@
 // pinned mailboxes, optional per-kernel timing, a fill kernel and a
 // device-wide exclusive scan.
 #include <algorithm>
+#include <atomic>
 #include <map>
 #include <mutex>
 
@@ -182,6 +183,8 @@ Workspace& Workspace::get(hipStream_t s) {
     for (auto& kv : all)
         if (kv.first.first == dev && kv.first.second == s) return *kv.second;
     all.push_back({{dev, s}, new Workspace(s)});
+    static std::atomic<uint32_t> places{0};  // teams of concurrent streams gather on different XCDs
+    all.back().second->place = places.fetch_add(1, std::memory_order_relaxed) % 8;
     return *all.back().second;
 }
 
@@ -282,13 +285,13 @@ Mailbox& Mailbox::get() {
 
 HostSlots::HostSlots() {
     void* p = nullptr;
-    EVQ_HIP(hipHostMalloc(&p, kSlots * sizeof(uint32_t),
+    EVQ_HIP(hipHostMalloc(&p, kWords * sizeof(unsigned long long),
                           hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable));
-    h_ = static_cast<uint32_t*>(p);
-    for (uint32_t i = 0; i < kSlots; ++i) h_[i] = kEmpty;
+    h_ = static_cast<unsigned long long*>(p);
+    for (uint32_t i = 0; i < kWords; ++i) h_[i] = kEmpty;
     void* d = nullptr;
     EVQ_HIP(hipHostGetDevicePointer(&d, p, 0));
-    d_ = static_cast<uint32_t*>(d);
+    d_ = static_cast<unsigned long long*>(d);
 }
 
 HostSlots& HostSlots::get() {
@@ -373,7 +376,7 @@ uint64_t launch_depth() { return tuning().launch_depth; }
 
 bool trace_loops() { return tuning().trace_loops != 0; }
 
-void wait_slot(volatile uint32_t* slot, hipStream_t s, const char* what) {
+void wait_slot(volatile unsigned long long* slot, hipStream_t s, const char* what) {
     if (__atomic_load_n(slot, __ATOMIC_ACQUIRE) != HostSlots::kEmpty) return;
     const auto t0 = std::chrono::steady_clock::now();
     auto next_check = t0 + std::chrono::microseconds(200);

@@ -17,7 +17,8 @@
 //               dense iterations of the full-window intersection solve the
 //               expansion pulls instead (every vertex over its in-edges); in
 //               sparse ones it lists the next frontier itself and the next
-//               compaction skips its scan.
+//               compaction skips its scan; while the list is small a team of
+//               that compaction's blocks runs iteration after iteration.
 // Values improve with fire-and-forget uint32 atomicMin/atomicMax after a plain
 // read shows the candidate is better; improved vertices set their bit.
 #include "bounds.h"
@@ -39,6 +40,9 @@ constexpr int kBlock = 256;
 #define EVQ_NT_EDGES 0
 #endif
 constexpr uint32_t kExpandBlocks = EVQ_EXPAND_BLOCKS;
+// Largest list that a team runs: a tile of 512 edges for each of its 64 blocks
+// (65536 measured the same).
+constexpr uint32_t kTeamEdges = 32768;
 constexpr int kWalkers = EVQ_WALKERS;
 
 template <typename T>
@@ -72,6 +76,9 @@ struct SolveArgs {
     uint32_t append_edges;
     uint32_t append_items;  // ... or at most this many frontier vertices (0: never)
     FrontierCounters* cnt;
+    Team* team;
+    uint32_t team_edges;  // a list of at most this many edges is left to a team (0: never)
+    uint32_t place;       // the team's eighth of the grid's blocks
     unsigned long long* stats;
     uint32_t V;
     // pull step (full-window intersection only): reverse CSR and the share of
@@ -130,6 +137,134 @@ __device__ __forceinline__ void count_visits(const SolveArgs& a, uint32_t n) {
     if (lane_id() == 0 && s) atomicAdd(&a.stats[0], (unsigned long long)s);
 }
 
+// An appending expansion's improved vertices: the first lane to improve a
+// vertex in this iteration (it moves the vertex's stamp to this iteration's
+// epoch) lists it for the next iteration, if it has edges in this solve's
+// graph.  True where this lane lists v; then rb, deg and sp are its row.
+template <int MODE>
+__device__ __forceinline__ bool first_to_improve(const SolveArgs& a, bool improved, uint32_t v, uint32_t epoch,
+                                                 uint32_t& rb, uint32_t& deg, uint32_t& sp) {
+    rb = deg = sp = 0;
+    if (improved && atomicMax(&a.stamp[v], epoch) != epoch) {
+        rb = a.row_ptr[v];
+        deg = row_end<MODE>(a, v) - rb;
+        if (MODE != 0) sp = a.row_split[v];
+    }
+    return deg != 0;
+}
+
+// One iteration of a team: list q, (items << 32) | edges = x, into list q ^ 1.
+// Each member takes an equal slice of the edges, a tile of 512 (one per thread)
+// at a time; lists and values, which the other members write, are read past the
+// L1.  The tile's vertices are reserved with one atomic for the whole block:
+// with one per wave, the same-address atomics (11 ns each) took more than the
+// rest of the iteration.
+template <int A, int MODE, int MW, bool ST>
+__device__ __forceinline__ void team_step(const SolveArgs& a, const Mask<MW>& W, const TeamRun& r, int q,
+                                          unsigned long long x, unsigned long long* count, uint32_t epoch) {
+    __shared__ uint32_t s_items[kCompactBlock / 64], s_edges[kCompactBlock / 64], s_base[2];
+    const uint32_t n = items_of(x), T = edges_of(x);
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t Rb = ((T + r.n - 1) / r.n + kCompactBlock - 1) / kCompactBlock * kCompactBlock;  // T is at most team_edges
+    const uint32_t b0 = r.rank * Rb, b1 = b0 + Rb < T ? b0 + Rb : T;
+    for (uint32_t tile = b0; tile < b1; tile += kCompactBlock) {
+        const uint32_t base = tile + wave * 64;
+        bool want = false;
+        uint32_t v = 0;
+        if (base < b1) {
+            const uint32_t cur = wave_search<true>(a.fo[q], n, base);
+            const uint32_t idx = cur + lane;
+            uint32_t off = 0xFFFFFFFFu, dl = 0, sp = 0, u = 0;
+            if (idx < n) {
+                off = shared_load(a.fo[q] + idx);
+                dl = shared_load(a.fd[q] + idx);
+                if (MODE != 0) sp = shared_load(a.fs[q] + idx);
+                u = shared_load(a.fv[q] + idx);
+            }
+            const uint32_t xv = off <= base + 63 ? shared_load(a.R + u) : 0u;
+            const uint32_t t = base + lane;
+            int o = 0;
+#pragma unroll
+            for (int step = 32; step >= 1; step >>= 1) {
+                const uint32_t y = __shfl(off, o + step, 64);
+                if (y <= t) o += step;
+            }
+            const uint32_t e = t + __shfl(dl, o, 64);
+            const uint32_t split = MODE != 0 ? __shfl(sp, o, 64) : 0u;
+            const uint32_t val = __shfl(xv, o, 64);
+            want = t < b1;
+            if (want && MODE != 0 && e >= split) want = partial_in<MODE, MW>(a.mask, e, W);
+            if (want) {
+                v = a.col[e];
+                const uint32_t cand = Alg<A>::extend(val, a.wgt[e]);
+                want = Alg<A>::better(cand, shared_load(a.R + v));
+                if (want) Alg<A>::improve_nr(&a.R[v], cand);
+            }
+            count_visits<ST>(a, t < b1 ? 1u : 0u);
+            if (ST) {
+                const uint32_t su = wave_sum(want ? 1u : 0u);
+                if (lane == 0 && su) atomicAdd(&a.stats[4], (unsigned long long)su);
+            }
+        }
+        uint32_t rb, deg, sp;
+        const bool app = first_to_improve<MODE>(a, want, v, epoch, rb, deg, sp);
+        const uint64_t bal = __ballot(app);
+        const uint32_t incl = wave_incl_scan(deg);
+        if (lane == 63) {
+            s_items[wave] = (uint32_t)__popcll(bal);
+            s_edges[wave] = incl;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t ni = 0, ne = 0;
+            for (int w = 0; w < kCompactBlock / 64; ++w) {
+                ni += s_items[w];
+                ne += s_edges[w];
+            }
+            const unsigned long long at = ni ? atomicAdd(count, ((unsigned long long)ni << 32) | ne) : 0ull;
+            s_base[0] = items_of(at);
+            s_base[1] = edges_of(at);
+        }
+        __syncthreads();
+        if (app) {
+            uint32_t item = s_base[0] + (uint32_t)__popcll(bal & lanemask_lt());
+            uint32_t edge = s_base[1] + incl - deg;
+            for (uint32_t w = 0; w < wave; ++w) {
+                item += s_items[w];
+                edge += s_edges[w];
+            }
+            shared_store(a.fo[q ^ 1] + item, edge);
+            shared_store(a.fd[q ^ 1] + item, rb - edge);
+            if (MODE != 0) shared_store(a.fs[q ^ 1] + item, sp);
+            shared_store(a.fv[q ^ 1] + item, v);
+        }
+        __syncthreads();  // the counts are read until here
+    }
+}
+
+// A team's launch: iterations from list p (count x) on, until the list is
+// empty, has more than team_edges edges (the launches take over again), or
+// kTeamIters have been run.  Epochs epoch .. epoch + kTeamIters - 1 are its own.
+template <int A, int MODE, int MW, bool ST>
+__device__ __forceinline__ void team_iterations(const SolveArgs& a, const Mask<MW>& W, int h, int p,
+                                                unsigned long long x, uint32_t epoch, unsigned long long* slot) {
+    TeamRun r;
+    if (!team_join(a.team, a.place, r)) return;
+    uint32_t k = 0, items = 0;
+    int q = p;
+    for (;;) {
+        team_step<A, MODE, MW, ST>(a, W, r, q, x, &a.team->packed[(k + 1) % 3], epoch + k);
+        if (r.rank == 0 && threadIdx.x == 0) shared_store(&a.team->packed[(k + 2) % 3], 0ull);
+        items += items_of(x);
+        ++k;
+        q ^= 1;
+        if (!team_barrier(a.team, r)) return;
+        x = shared_load(&a.team->packed[k % 3]);
+        if (x == 0 || edges_of(x) > a.team_edges || k == kTeamIters) break;
+    }
+    if (r.rank == 0 && threadIdx.x == 0) team_leave(a.cnt, a.team, epoch, h, q, x, items, k, slot);
+}
+
 // Flags -> frontier items of parity p, clearing the flags it reads; vertices
 // without edges in this solve's graph are dropped.
 // With near/far scheduling on (delta > 0), a vertex whose order key (its
@@ -151,9 +286,15 @@ __device__ __forceinline__ void count_visits(const SolveArgs& a, uint32_t n) {
 // edge of the bucket lands above the bound), so the heavy edges of the waiting
 // vertices are expanded once, in the same iteration as the light edges of the
 // next bucket, which spans the width above the smallest value still flagged.
-template <int A, int MODE>
-__global__ void __launch_bounds__(kCompactBlock) k_compact_frontier(SolveArgs a, int p, int first) {
+// Where the list is there already (the expansion before appended it, a team
+// left it, or the solve's start listed the source) there is nothing to scan,
+// and a small list is run by a team of this launch's blocks.
+template <int A, int MODE, int MW, bool ST>
+__global__ void __launch_bounds__(kCompactBlock)
+    k_compact_frontier(SolveArgs a, Mask<MW> W, int h, uint32_t first, uint32_t epoch, unsigned long long* slot) {
     FrontierCounters* const c = a.cnt;
+    const int p = h ^ (int)uniform(c->flip[h]);
+    const uint32_t status = first ? first : c->status[h];
     const bool lh = a.nheavy != nullptr;
     uint32_t bt = 0xFFFFFFFFu;  // bucket bound: light edges of flagged vertices below it are expanded
     bool ended = false;         // the previous bucket ended: its waiting heavy edges are expanded
@@ -168,7 +309,15 @@ __global__ void __launch_bounds__(kCompactBlock) k_compact_frontier(SolveArgs a,
             }
         }
     }
-    const bool skip = compaction_skips(c, p, first);
+    if (a.team_edges && epoch && (status & 6u) && c->delta == 0 && !lh) {
+        const unsigned long long x = (status & 4u) ? a.team->result : c->packed[p];
+        if (x && edges_of(x) <= a.team_edges) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) c->packed[p ^ 1] = 0ull;
+            team_iterations<A, MODE, MW, ST>(a, W, h, p, x, epoch, slot);
+            return;
+        }
+    }
+    const bool skip = compaction_skips(c, p, status, a.team);
     if (lh && blockIdx.x == 0 && threadIdx.x == 0) c->bthr[p] = bt;
     if (skip) return;
     const uint32_t thr = c->thr;
@@ -370,44 +519,41 @@ __device__ __forceinline__ void pull_walk(const SolveArgs& a, uint32_t T) {
     }
 }
 
-// An appending expansion's improved vertices: the first lane to improve a
-// vertex in this iteration (it moves the vertex's stamp to this iteration's
-// epoch) lists it for the next iteration, if it has edges in this solve's
-// graph.  The wave reserves its items and their edges with one packed atomic
-// on the next parity's counter, so the list's running edge offsets ascend
-// with the item index as a compaction's do.  Every lane of the wave calls it.
+// The wave reserves its items and their edges with one packed atomic on the
+// list's counter, so the list's running edge offsets ascend with the item
+// index as a compaction's do.  The items go to set q.  Every lane of the wave
+// calls it.
 template <int MODE>
-__device__ __forceinline__ void append_next(const SolveArgs& a, int p, bool improved, uint32_t v, uint32_t epoch) {
-    bool app = false;
-    uint32_t rb = 0, deg = 0, sp = 0;
-    if (improved && atomicMax(&a.stamp[v], epoch) != epoch) {
-        rb = a.row_ptr[v];
-        deg = row_end<MODE>(a, v) - rb;
-        if (MODE != 0) sp = a.row_split[v];
-        app = deg != 0;
-    }
+__device__ __forceinline__ void append_next(const SolveArgs& a, int q, unsigned long long* count, bool improved,
+                                            uint32_t v, uint32_t epoch) {
+    uint32_t rb, deg, sp;
+    const bool app = first_to_improve<MODE>(a, improved, v, epoch, rb, deg, sp);
     const uint64_t bal = __ballot(app);
     if (!bal) return;
-    if (!app) deg = 0;
     const uint32_t incl = wave_incl_scan(deg);
     const uint32_t tot = lane_value(incl, 63);
     unsigned long long base = 0;
-    if (lane_id() == 0) base = atomicAdd(&a.cnt->packed[p ^ 1], ((unsigned long long)__popcll(bal) << 32) | tot);
+    if (lane_id() == 0) base = atomicAdd(count, ((unsigned long long)__popcll(bal) << 32) | tot);
     const uint32_t bi = lane_value((uint32_t)(base >> 32), 0);
     const uint32_t be = lane_value((uint32_t)base, 0);
     if (app) {
         const uint32_t item = bi + (uint32_t)__popcll(bal & lanemask_lt());
         const uint32_t edge = be + incl - deg;
-        a.fo[p ^ 1][item] = edge;
-        a.fd[p ^ 1][item] = rb - edge;
-        if (MODE != 0) a.fs[p ^ 1][item] = sp;
-        a.fv[p ^ 1][item] = v;
+        a.fo[q][item] = edge;
+        a.fd[q][item] = rb - edge;
+        if (MODE != 0) a.fs[q][item] = sp;
+        a.fv[q][item] = v;
     }
 }
 
 template <int A, int MODE, int MW, bool ST>
-__global__ void __launch_bounds__(kBlock) k_expand(SolveArgs a, Mask<MW> W, int p, uint32_t epoch, uint32_t* slot) {
+__global__ void __launch_bounds__(kBlock)
+    k_expand(SolveArgs a, Mask<MW> W, int h, uint32_t epoch, unsigned long long* slot) {
     constexpr int NW = kWalkers;
+    const bool ran = epoch && a.team->ran == epoch;  // a team ran this iteration and published
+    if (blockIdx.x == 0 && threadIdx.x == 0) team_reset(a.team);  // for the next compaction
+    if (ran) return;
+    const int p = h ^ (int)uniform(a.cnt->flip[h]);
     const unsigned long long c0 = a.cnt->packed[p];
     bool pull = false;
     if (MODE == 0 && a.pull_frac != kNone) {
@@ -418,8 +564,8 @@ __global__ void __launch_bounds__(kBlock) k_expand(SolveArgs a, Mask<MW> W, int 
     const bool small = (a.append_edges && edges_of(c0) <= a.append_edges) ||
                        (a.append_items && items_of(c0) <= a.append_items);
     const bool lh = a.nheavy != nullptr;
-    const bool appends = !pull && small && a.cnt->delta == 0 && !lh;
-    const unsigned long long cx = expand_prologue(a.cnt, p, slot, appends);
+    const bool appends = !pull && small && a.cnt->delta == 0 && !lh && epoch != 0;
+    const unsigned long long cx = expand_prologue(a.cnt, h, p, slot, appends);
     const uint32_t n = items_of(cx), T = edges_of(cx);
     if (T == 0) return;
     if (pull) {
@@ -509,7 +655,8 @@ __global__ void __launch_bounds__(kBlock) k_expand(SolveArgs a, Mask<MW> W, int 
                     else amin = k < amin ? k : amin;
                 }
             }
-            if (appends) append_next<MODE>(a, p, st[j].want, st[j].v, epoch);
+            if (appends)
+                append_next<MODE>(a, p ^ 1, &a.cnt->packed[p ^ 1], st[j].want, st[j].v, epoch);
         }
         if (lh) {
             if (!near_told && __ballot(below)) {
@@ -541,27 +688,69 @@ __global__ void __launch_bounds__(kBlock) k_expand(SolveArgs a, Mask<MW> W, int 
         atomicMin(&a.cnt->nmin[p], above);
 }
 
-// Start of a solve: the threshold starts one step above the best key.
-// With a bucket width (bdelta > 0), the first bucket spans the width above
-// the source's key, and the first compaction reads it as unfinished.
-__global__ void k_solve_start(FrontierCounters* c, uint32_t delta, uint32_t heavy, uint32_t* R, uint8_t* flags,
-                              uint32_t source, uint32_t at_source, uint32_t bdelta, uint32_t first_bound) {
-    if (threadIdx.x == 0) {
-        c->delta = delta;
-        c->heavy = delta ? heavy : 0u;
-        c->thr = delta ? delta : 0xFFFFFFFFu;
-        c->far[0] = c->far[1] = 0u;
-        c->fmin[0] = c->fmin[1] = 0xFFFFFFFFu;
-        c->kall[0] = c->kall[1] = 0xFFFFFFFFu;
-        c->bdelta = bdelta;
-        c->bthr[0] = c->bthr[1] = bdelta ? first_bound : 0xFFFFFFFFu;
-        c->near[0] = c->near[1] = 1u;
-        c->nmin[0] = c->nmin[1] = 0xFFFFFFFFu;
-        if (R) {
-            R[source] = at_source;
-            flags[source] = 1;
+// Counters at the start of a solve: the threshold starts one step above the
+// best key; with a bucket width (bdelta > 0) the first bucket spans the width
+// above the source's key, and the first compaction reads it as unfinished.
+struct StartArgs {
+    uint32_t delta, heavy, bdelta, first_bound;
+    uint32_t zero_stats;      // first solve of a query: the statistics start
+    unsigned long long* aux;  // scratch counters of the reduction, cleared for it
+};
+
+__device__ __forceinline__ void start_counters(const SolveArgs& a, const StartArgs& st) {
+    FrontierCounters* const c = a.cnt;
+    c->delta = st.delta;
+    c->heavy = st.delta ? st.heavy : 0u;
+    c->thr = st.delta ? st.delta : 0xFFFFFFFFu;
+    c->far[0] = c->far[1] = 0u;
+    c->fmin[0] = c->fmin[1] = 0xFFFFFFFFu;
+    c->kall[0] = c->kall[1] = 0xFFFFFFFFu;
+    c->bdelta = st.bdelta;
+    c->bthr[0] = c->bthr[1] = st.bdelta ? st.first_bound : 0xFFFFFFFFu;
+    c->near[0] = c->near[1] = 1u;
+    c->nmin[0] = c->nmin[1] = 0xFFFFFFFFu;
+    c->packed[0] = c->packed[1] = 0ull;
+    c->flip[0] = c->flip[1] = 0u;
+    c->status[0] = c->status[1] = 0u;
+    team_reset(a.team);
+    a.team->ran = 0u;  // the tags may start again
+    if (st.zero_stats)
+        for (int i = 0; i < 8; ++i) a.stats[i] = 0ull;
+    for (int i = 0; i < 4; ++i) st.aux[i] = 0ull;
+}
+
+// Intersection solve, first step (its first iteration has host parity h): every
+// value unreached but the source's, and the source's flag set or, with `rend`
+// (the rows' ends in this solve's graph), the source put into item set h
+// itself, so that the first iteration needs no compaction.
+__global__ void __launch_bounds__(256) k_cap_start(SolveArgs a, StartArgs st, int h, uint32_t source,
+                                                   uint32_t unreached, uint32_t at_source,
+                                                   const uint32_t* __restrict__ rend) {
+    for (uint64_t v = blockIdx.x * 256ull + threadIdx.x; v < a.V; v += gridDim.x * 256ull)
+        a.R[v] = v == source ? at_source : unreached;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        start_counters(a, st);
+        if (!rend) {
+            a.flags[source] = 1;
+        } else {
+            const uint32_t rb = a.row_ptr[source], deg = rend[source] - rb;
+            a.fo[h][0] = 0u;
+            a.fd[h][0] = rb;
+            a.fs[h][0] = a.row_split[source];
+            a.fv[h][0] = source;
+            if (deg) a.cnt->packed[h] = (1ull << 32) | deg;
         }
     }
+}
+
+// Union solve, start: R takes the intersection's values (4 per thread where both are aligned).
+__global__ void __launch_bounds__(256) k_cup_start(SolveArgs a, StartArgs st, const uint32_t* __restrict__ rcap) {
+    const uint64_t i0 = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
+    const bool al = (((uintptr_t)rcap | (uintptr_t)a.R) & 15) == 0;
+    const uint64_t n4 = al ? a.V / 4 : 0;
+    for (uint64_t i = i0; i < n4; i += step) reinterpret_cast<uint4*>(a.R)[i] = reinterpret_cast<const uint4*>(rcap)[i];
+    for (uint64_t i = n4 * 4 + i0; i < a.V; i += step) a.R[i] = rcap[i];
+    if (blockIdx.x == 0 && threadIdx.x == 0) start_counters(a, st);
 }
 
 // Union solve, first step: relax every edge present in some but not all
@@ -600,16 +789,20 @@ __global__ void __launch_bounds__(kBlock) k_seed_partial(SolveArgs a, Mask<MW> W
     }
 }
 
+// listed: the first frontier is in the item set already (k_solve_start).
 template <int A, int MODE, int MW, bool ST>
-uint64_t frontier_loop(SolveArgs a, const Mask<MW>& W, Frontier& f, hipStream_t s, uint64_t max_iters) {
-    const uint32_t cblocks = grid_for(a.V, kCompactIds, 4096);
+uint64_t frontier_loop(SolveArgs a, const Mask<MW>& W, Frontier& f, hipStream_t s, uint64_t max_iters,
+                       bool listed = false) {
+    uint32_t cblocks = grid_for(a.V, kCompactIds, 4096);
+    if (a.team_edges && cblocks < 8 * kTeamBlocks) cblocks = 8 * kTeamBlocks;  // room for a whole team
     static const char* names[3] = {"solve_expand_cap_all", "solve_expand_cap", "solve_expand_cup"};
-    auto issue = [&](uint64_t, int p, bool first, uint32_t* slot) {
-        const uint32_t epoch = ++*f.epoch;
-        EVQ_LAUNCH("solve_compact", (k_compact_frontier<A, MODE>), cblocks, kCompactBlock, s, a, p, first ? 1 : 0);
+    auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
+        const uint32_t epoch = take_epochs(f);
+        EVQ_LAUNCH("solve_compact", (k_compact_frontier<A, MODE, MW, ST>), cblocks, kCompactBlock, s, a, W, p,
+                   first ? (listed ? 3u : 1u) : 0u, epoch, slot);
         EVQ_LAUNCH(names[MODE], (k_expand<A, MODE, MW, ST>), kExpandBlocks, kBlock, s, a, W, p, epoch, slot);
     };
-    return drive_loop(issue, f.p, s, max_iters, "bound solve", &f.items);
+    return drive_loop(issue, f.p, s, max_iters, "bound solve", &f.items, a.team_edges ? kTeamDepth : 0);
 }
 
 template <int MW>
@@ -640,6 +833,9 @@ SolveArgs make_args(const Graph& g, const Frontier& f, uint32_t* R) {
     a.append_edges = f.append_edges;
     a.append_items = f.append_items;
     a.cnt = f.cnt;
+    a.team = f.team;
+    a.team_edges = f.append_edges < kTeamEdges ? f.append_edges : kTeamEdges;
+    a.place = f.place;
     a.stats = f.stats;
     a.V = g.V;
     a.rv_src = a.rv_w = a.rv_dst = a.rv_cnt = nullptr;
@@ -651,7 +847,6 @@ SolveArgs make_args(const Graph& g, const Frontier& f, uint32_t* R) {
 template <int A, int MW, bool ST>
 uint64_t solve_cap_t(const Graph& g, const Window& W, uint32_t source, uint32_t* R, Frontier& f, hipStream_t s) {
     SolveArgs a = make_args(g, f, R);
-    fill_u32(R, g.V, Alg<A>::unreached, s);
     // the bucketed schedule needs additive weights (SSSP); it replaces near/far and the pull step
     uint32_t bd = 0;
     if (A == EVQ_SSSP && f.bdelta && g.E) {
@@ -665,8 +860,12 @@ uint64_t solve_cap_t(const Graph& g, const Window& W, uint32_t source, uint32_t*
     const uint32_t fd = bd ? 0u : f.delta;
     // a guard against runaway loops: a bucket end takes an iteration of its own at most once per vertex
     const uint64_t cap = bd ? 4ull * g.V + 16 : (uint64_t)g.V + 2;
-    EVQ_LAUNCH("solve_start", k_solve_start, 1, 64, s, f.cnt, fd, f.heavy, R, f.flags, source, Alg<A>::at_source,
-               bd, bd ? order_key<A>(Alg<A>::at_source) + bd : 0u);
+    const bool listed = !fd && !bd;
+    const uint32_t* rend = W.full ? g.row_split : g.row_ptr + 1;
+    const StartArgs st{fd, f.heavy, bd, bd ? order_key<A>(Alg<A>::at_source) + bd : 0u, f.fresh ? 1u : 0u, f.aux};
+    f.fresh = false;
+    EVQ_LAUNCH("solve_start", k_cap_start, grid_for(g.V, 256 * 8, 2048), 256, s, a, st, f.p, source,
+               Alg<A>::unreached, Alg<A>::at_source, listed ? rend : (const uint32_t*)nullptr);
     if (W.full) {
         const uint32_t pf = fd == 0 && !bd && g.E && g.E < (1ull << 30) && g.V < (1u << 30) ? pull_frac() : kNone;
         if (pf != kNone && reverse_ready(g, s)) {
@@ -676,16 +875,17 @@ uint64_t solve_cap_t(const Graph& g, const Window& W, uint32_t source, uint32_t*
             a.rv_cnt = g.rv_cnt;
             a.pull_frac = pf;
         }
-        return frontier_loop<A, 0, MW, ST>(a, window_mask<MW>(W), f, s, cap);
+        return frontier_loop<A, 0, MW, ST>(a, window_mask<MW>(W), f, s, cap, listed);
     }
-    return frontier_loop<A, 1, MW, ST>(a, window_mask<MW>(W), f, s, cap);
+    return frontier_loop<A, 1, MW, ST>(a, window_mask<MW>(W), f, s, cap, listed);
 }
 
 template <int A, int MW, bool ST>
-uint64_t solve_cup_t(const Graph& g, const Window& W, uint32_t* R, Frontier& f, hipStream_t s) {
+uint64_t solve_cup_t(const Graph& g, const Window& W, const uint32_t* rcap, uint32_t* R, Frontier& f, hipStream_t s) {
     SolveArgs a = make_args(g, f, R);
-    EVQ_LAUNCH("solve_start", k_solve_start, 1, 64, s, f.cnt, f.delta, f.heavy, (uint32_t*)nullptr, f.flags, 0u,
-               0u, 0u, 0u);
+    EVQ_LAUNCH("solve_start", k_cup_start, grid_for((g.V + 3) / 4, 256 * 4, 2048), 256, s, a,
+               (StartArgs{f.delta, f.heavy, 0u, 0u, 0u, f.aux}), rcap);
+    f.aux_clear = true;
     if (g.n_partial)
         EVQ_LAUNCH("solve_seed_partial", (k_seed_partial<A, MW, ST>), grid_for(g.n_partial, kBlock, 16384), kBlock, s,
                    a, window_mask<MW>(W), g.p_src, g.p_dst, g.p_w, g.p_mask, (uint32_t)g.n_partial);
@@ -705,19 +905,23 @@ uint64_t dispatch_cap(uint32_t algo, const Graph& g, const Window& W, uint32_t s
 }
 
 template <int MW, bool ST>
-uint64_t dispatch_cup(uint32_t algo, const Graph& g, const Window& W, uint32_t* R, Frontier& f, hipStream_t s) {
+uint64_t dispatch_cup(uint32_t algo, const Graph& g, const Window& W, const uint32_t* rcap, uint32_t* R, Frontier& f,
+                      hipStream_t s) {
     switch (algo) {
-    case EVQ_SSSP: return solve_cup_t<EVQ_SSSP, MW, ST>(g, W, R, f, s);
-    case EVQ_BFS: return solve_cup_t<EVQ_BFS, MW, ST>(g, W, R, f, s);
-    case EVQ_SSWP: return solve_cup_t<EVQ_SSWP, MW, ST>(g, W, R, f, s);
-    case EVQ_SSNP: return solve_cup_t<EVQ_SSNP, MW, ST>(g, W, R, f, s);
-    default: return solve_cup_t<EVQ_VITERBI, MW, ST>(g, W, R, f, s);
+    case EVQ_SSSP: return solve_cup_t<EVQ_SSSP, MW, ST>(g, W, rcap, R, f, s);
+    case EVQ_BFS: return solve_cup_t<EVQ_BFS, MW, ST>(g, W, rcap, R, f, s);
+    case EVQ_SSWP: return solve_cup_t<EVQ_SSWP, MW, ST>(g, W, rcap, R, f, s);
+    case EVQ_SSNP: return solve_cup_t<EVQ_SSNP, MW, ST>(g, W, rcap, R, f, s);
+    default: return solve_cup_t<EVQ_VITERBI, MW, ST>(g, W, rcap, R, f, s);
     }
 }
 
-__global__ void k_init_frontier(FrontierCounters* c, unsigned long long* st, int n) {
+__global__ void k_init_frontier(FrontierCounters* c, Team* team, unsigned long long* st, int n) {
     if (threadIdx.x == 0) {
+        team_reset(team);
+        team->ran = 0u;
         c->packed[0] = c->packed[1] = 0ull;
+        c->flip[0] = c->flip[1] = 0u;
         c->status[0] = c->status[1] = 0u;
         c->far[0] = c->far[1] = 0u;
         c->fmin[0] = c->fmin[1] = 0xFFFFFFFFu;
@@ -747,7 +951,7 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
     // stamps below every epoch to come: cleared where the buffer is new, where this graph has more
     // vertices than any before it on the buffer (a buffer is larger than what was asked for, and the
     // rest of it is unset), and before the epoch counter wraps
-    if (ws.stamps_known < g.V || ws.epoch > 0xFFFF0000u) {
+    if (ws.stamps_known < g.V || ws.epoch > 0xC0000000u) {
         fill_u32(f.stamp, g.V, 0u, s);
         ws.stamps_known = g.V;
         ws.epoch = 0;
@@ -758,7 +962,9 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
         f.append_edges = tn.append_edges;
         f.append_items = tn.append_items;
     }
-    char* ctl = ws.buf<char>(Workspace::kControl, 512);
+    char* ctl = ws.buf<char>(Workspace::kControl, 512 + kTeamBytes);
+    f.team = reinterpret_cast<Team*>(ctl + 512);
+    f.place = ws.place;
     f.cnt = reinterpret_cast<FrontierCounters*>(ctl);
     f.stats = reinterpret_cast<unsigned long long*>(ctl + 128);
     f.aux = reinterpret_cast<unsigned long long*>(ctl + 256);
@@ -771,9 +977,13 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
         ws.flags_clear = nflag;
     }
     ws.in_use = true;
-    EVQ_LAUNCH("query_init", k_init_frontier, 1, 64, s, f.cnt, f.stats, 8);
     f.p = 0;
     return f;
+}
+
+void init_frontier(Frontier& f, hipStream_t s) {
+    EVQ_LAUNCH("query_init", k_init_frontier, 1, 64, s, f.cnt, f.team, f.stats, 8);
+    f.fresh = false;
 }
 
 uint64_t solve_cap(const Graph& g, uint32_t algo, const Window& W, uint32_t source, uint32_t* R, Frontier& f,
@@ -784,10 +994,12 @@ uint64_t solve_cap(const Graph& g, uint32_t algo, const Window& W, uint32_t sour
                  : dispatch_cap<2, false>(algo, g, W, source, R, f, s);
 }
 
-uint64_t solve_cup(const Graph& g, uint32_t algo, const Window& W, uint32_t* R, Frontier& f, hipStream_t s,
-                   bool stats) {
-    if (g.MW == 1) return stats ? dispatch_cup<1, true>(algo, g, W, R, f, s) : dispatch_cup<1, false>(algo, g, W, R, f, s);
-    return stats ? dispatch_cup<2, true>(algo, g, W, R, f, s) : dispatch_cup<2, false>(algo, g, W, R, f, s);
+uint64_t solve_cup(const Graph& g, uint32_t algo, const Window& W, const uint32_t* rcap, uint32_t* R, Frontier& f,
+                   hipStream_t s, bool stats) {
+    if (g.MW == 1) return stats ? dispatch_cup<1, true>(algo, g, W, rcap, R, f, s)
+                                : dispatch_cup<1, false>(algo, g, W, rcap, R, f, s);
+    return stats ? dispatch_cup<2, true>(algo, g, W, rcap, R, f, s)
+                 : dispatch_cup<2, false>(algo, g, W, rcap, R, f, s);
 }
 
 }  // namespace evq
