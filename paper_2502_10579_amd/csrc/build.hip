@@ -1320,15 +1320,16 @@ void build_reverse(const Graph& g, hipStream_t s) {
 
 namespace {
 
-// Runs f(0) .. f(n - 1) on up to 8 host threads (this one among them); f must
-// not throw.  A thread that cannot be started leaves its share to the others.
+// Runs f(0) .. f(n - 1) on up to 8 host threads, at most `worth` of them (this
+// one among them: starting seven takes 0.3 ms); f must not throw.  A thread that
+// cannot be started leaves its share to the others.
 template <typename F>
-void on_threads(uint64_t n, F f) {
+void on_threads(uint64_t n, uint64_t worth, F f) {
     std::atomic<uint64_t> next{0};
     auto work = [&] {
         for (uint64_t i; (i = next.fetch_add(1, std::memory_order_relaxed)) < n;) f(i);
     };
-    const uint64_t nt = std::min<uint64_t>(n, std::min(8u, std::max(1u, std::thread::hardware_concurrency())));
+    const uint64_t nt = std::min<uint64_t>(std::min(n, worth), std::min(8u, std::max(1u, std::thread::hardware_concurrency())));
     std::vector<std::thread> th;
     try {
         for (uint64_t t = 1; t < nt; ++t) th.emplace_back(work);
@@ -1361,8 +1362,10 @@ uint32_t check_spans(const std::vector<Span>& spans, uint32_t V) {
             pieces.push_back({i, a, std::min(spans[i].n, a + kCheckEdges)});
     }
     std::vector<uint32_t> maxw(pieces.size() + 1, 1u);
+    uint64_t total = 0;
+    for (const Span& sp : spans) total += sp.n;
     std::atomic<uint64_t> first_bad{pieces.size()};
-    on_threads(pieces.size(), [&](uint64_t k) {
+    on_threads(pieces.size(), total / kCheckEdges, [&](uint64_t k) {
         const evq_edge* e = spans[pieces[k].span].e;
         uint32_t bad = 0, mw = 1;
         for (uint64_t i = pieces[k].lo; i < pieces[k].hi; ++i) {
