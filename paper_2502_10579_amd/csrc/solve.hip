@@ -759,20 +759,24 @@ template <int A, int MW, bool ST>
 __global__ void __launch_bounds__(kBlock) k_seed_partial(SolveArgs a, Mask<MW> W, const uint32_t* __restrict__ p_src,
                                                          const uint32_t* __restrict__ p_dst,
                                                          const uint32_t* __restrict__ p_w,
-                                                         const uint64_t* __restrict__ p_mask, uint32_t n_partial) {
+                                                         const uint64_t* __restrict__ p_mask, uint32_t n_partial,
+                                                         int full) {
     const uint32_t stride = gridDim.x * kBlock;
     for (uint32_t base = blockIdx.x * kBlock; base < n_partial; base += stride) {
         const uint32_t q = base + threadIdx.x;
         bool act = false;
         if (q < n_partial) {
-            Mask<MW> m = load_mask<MW>(p_mask, q);
-            bool any = false, all = true;
+            act = true;
+            if (!full) {  // every edge of the table is partial in the window of all snapshots
+                Mask<MW> m = load_mask<MW>(p_mask, q);
+                bool any = false, all = true;
 #pragma unroll
-            for (int j = 0; j < MW; ++j) {
-                any |= (m.w[j] & W.w[j]) != 0;
-                all &= (m.w[j] & W.w[j]) == W.w[j];
+                for (int j = 0; j < MW; ++j) {
+                    any |= (m.w[j] & W.w[j]) != 0;
+                    all &= (m.w[j] & W.w[j]) == W.w[j];
+                }
+                act = any && !all;
             }
-            act = any && !all;
             if (act) {
                 const uint32_t v = p_dst[q];
                 const uint32_t cand = Alg<A>::extend(a.R[p_src[q]], p_w[q]);
@@ -888,7 +892,7 @@ uint64_t solve_cup_t(const Graph& g, const Window& W, const uint32_t* rcap, uint
     f.aux_clear = true;
     if (g.n_partial)
         EVQ_LAUNCH("solve_seed_partial", (k_seed_partial<A, MW, ST>), grid_for(g.n_partial, kBlock, 16384), kBlock, s,
-                   a, window_mask<MW>(W), g.p_src, g.p_dst, g.p_w, g.p_mask, (uint32_t)g.n_partial);
+                   a, window_mask<MW>(W), g.p_src, g.p_dst, g.p_w, g.p_mask, (uint32_t)g.n_partial, W.full ? 1 : 0);
     return frontier_loop<A, 2, MW, ST>(a, window_mask<MW>(W), f, s, (uint64_t)g.V + 2);
 }
 
