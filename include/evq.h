@@ -361,7 +361,8 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *                 own bounds, to depth 4 (default 0: off).
  *   split_min     EVQ_SPLIT_MIN: smallest half (default 8, >= 1).
  *   launch_depth  EVQ_LAUNCH_DEPTH: frontier iterations kept in flight, 1..32
- *                 (default 3).
+ *                 (default 3).  Loops whose small iterations run many to a
+ *                 launch (see append_edges) keep one in flight.
  *   direct_tasks  EVQ_DIRECT_TASKS: reduced subgraphs of at most this many
  *                 relaxation tasks have them written by the frontier
  *                 compaction, larger ones by a kernel of their own (default
@@ -382,7 +383,8 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *                 has at most this many edges lists the next frontier itself
  *                 (each improved vertex once, by a per-vertex stamp) instead
  *                 of marking flags for a compaction to scan (default 131072;
- *                 0: never).
+ *                 0: never).  Runs of iterations with at most this many edges,
+ *                 and at most 32768, are done by one launch.
  *   append_items  EVQ_APPEND_ITEMS: ... likewise an iteration whose frontier
  *                 has at most this many vertices (default 0: never).
  *   relax_staged  EVQ_RELAX_STAGED: the multi-snapshot relaxation stages each
