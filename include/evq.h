@@ -412,6 +412,10 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *                 the graph holds the map both ways on the device (8 bytes
  *                 per vertex) and on the host (4).  Read by evq_build; later
  *                 versions (evq_append) keep their graph's numbering.
+ * The blocks that run small iterations together wait for one another at most
+ * EVQ_TEAM_SPINS polls (environment only, read once; default 2^24, seconds);
+ * a call in which such a wait runs out returns EVQ_EDEVICE and leaves no
+ * answer, and later calls start afresh.
  * evq_tuning_set: EVQ_EINVAL on NULL, launch_depth outside 1..32,
  * split_min == 0 or relax_staged not 0, 2 or 4; calls already running keep
  * the values they started with.

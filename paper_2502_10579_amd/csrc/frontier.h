@@ -30,8 +30,10 @@ namespace evq {
 
 // What an expansion publishes for the host, in one 64-bit word: the frontier
 // items it processed (low word), the iterations it ran, and whether the loop
-// is done (nothing was left to process, now or for the next launch).
+// is done (nothing was left to process, now or for the next launch) or has
+// failed (a team gave up, see Team).
 constexpr unsigned long long kSlotDone = 1ull << 63;
+constexpr unsigned long long kSlotFailed = 1ull << 62;
 __host__ __device__ inline unsigned long long slot_word(uint32_t items, uint32_t iters, bool done) {
     return (done ? kSlotDone : 0ull) | ((unsigned long long)iters << 32) | items;
 }
@@ -123,12 +125,19 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
 // stores and read-modify-writes, and a member's accesses have completed
 // (s_waitcnt) before it arrives at the barrier.  An agent-scope fence would do
 // as well but writes the L2 back (7.6 us a barrier against 1.3).
+//
+// Every wait is bounded.  A member whose wait runs out leaves, the others'
+// next wait runs out too, and the lists are then in no known state: the
+// expansion's launch that follows finds the team begun and not ended
+// (team_end) and reports it to the host, which fails the call, instead of
+// expanding them.
 struct Team {
     uint32_t reg;     // members registered; bit 31: closed
     uint32_t n;       // their number, once closed
     uint32_t err;     // a wait ran out
-    uint32_t ran;     // tag of the last launch that a team ran
-    uint32_t pad0[28];
+    uint32_t began;   // tag of the last launch whose list a team took
+    uint32_t ran;     // ... and of the last that a team ran to its end
+    uint32_t pad0[27];
     uint32_t arrive;  // barrier arrivals so far
     uint32_t pad1[31];
     uint32_t gen;     // barriers completed
@@ -140,7 +149,7 @@ struct Team {
 };
 constexpr uint32_t kTeamBlocks = 64;
 constexpr uint32_t kTeamIters = 1024;      // most iterations of one launch
-constexpr uint32_t kTeamSpins = 1u << 24;  // bound of every wait (seconds); past it the launch gives up
+constexpr uint32_t kTeamSpins = 1u << 24;  // polls of a wait (seconds); past them the member gives up
 constexpr uint64_t kTeamBytes = 1024;      // control bytes of a team
 static_assert(sizeof(Team) <= kTeamBytes, "team control block");
 
@@ -172,29 +181,54 @@ __device__ __forceinline__ void team_leave(FrontierCounters* c, Team* t, uint32_
     __hip_atomic_store(slot, slot_word(items, k, x == 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-struct TeamRun {
-    uint32_t rank, n, gen;
+// How the team of the launch tagged `tag` fared, read by the expansion's launch
+// after it: there was none (or tag is 0), it ran the iteration and published,
+// or it began and did not end.
+enum class TeamEnd { kNone, kRan, kGaveUp };
+__device__ __forceinline__ TeamEnd team_end(const Team* t, uint32_t tag) {
+    if (tag == 0 || t->began != tag) return TeamEnd::kNone;
+    return t->ran == tag ? TeamEnd::kRan : TeamEnd::kGaveUp;
+}
+
+// The launch at host parity h found that the team before it gave up; one
+// thread.  No list is left for the launches already issued.
+__device__ __forceinline__ void team_report(FrontierCounters* c, int h, unsigned long long* slot) {
+    c->packed[0] = c->packed[1] = 0ull;
+    c->status[h ^ 1] = 0u;
+    __hip_atomic_store(slot, kSlotFailed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What the host lays down for teams.
+struct TeamRules {
+    uint32_t place;  // which eighth of a grid's blocks are the candidates
+    uint32_t spins;  // polls of a wait before a member gives up
 };
 
-// Every thread of a block calls it; true for the members' blocks.  `lane8`
-// picks which eighth of the grid's blocks are the candidates.
-__device__ __forceinline__ bool team_join(Team* t, uint32_t lane8, TeamRun& r) {
+struct TeamRun {
+    uint32_t rank, n, gen, spins;
+};
+
+// Every thread of a block calls it; true for the members' blocks.  tag (not
+// 0): this launch's.
+__device__ __forceinline__ bool team_join(Team* t, const TeamRules& rules, uint32_t tag, TeamRun& r) {
     const uint32_t eighths = gridDim.x < 8u ? gridDim.x : 8u;
-    if (blockIdx.x % 8u != lane8 % eighths || blockIdx.x / 8u >= kTeamBlocks) return false;
+    const uint32_t lane8 = rules.place % eighths;
+    if (blockIdx.x % 8u != lane8 || blockIdx.x / 8u >= kTeamBlocks) return false;
     __shared__ uint32_t s_rank, s_n;
     if (threadIdx.x == 0) {
         uint32_t rank = kNone, n = 0;
         const uint32_t k = shared_load(&t->reg) >> 31 ? 1u << 31 : atomicAdd(&t->reg, 1u);
         if (!(k >> 31)) {
             rank = k;
-            const uint32_t want = (gridDim.x - lane8 % eighths + 7u) / 8u;
+            const uint32_t want = (gridDim.x - lane8 + 7u) / 8u;
             const uint32_t all = want < kTeamBlocks ? want : kTeamBlocks;
             if (k == 0) {
                 for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < all; ++i) __builtin_amdgcn_s_sleep(1);
                 n = atomicOr(&t->reg, 1u << 31);
+                t->began = tag;
                 shared_store(&t->n, n);
             } else {
-                for (uint32_t i = 0; i < kTeamSpins && n == 0; ++i) n = shared_load(&t->n);
+                for (uint32_t i = 0; i < rules.spins && n == 0; ++i) n = shared_load(&t->n);
                 if (n == 0) rank = kNone;
             }
         }
@@ -205,12 +239,13 @@ __device__ __forceinline__ bool team_join(Team* t, uint32_t lane8, TeamRun& r) {
     r.rank = s_rank;
     r.n = s_n;
     r.gen = 0;
+    r.spins = rules.spins;
     return r.rank != kNone;
 }
 
 // Barrier over the team; every thread of every member calls it.  False: a
-// member did not arrive in time (the caller leaves without publishing, which
-// the host reports as an error).
+// member did not arrive in time (the caller leaves without publishing; see
+// team_end).
 __device__ __forceinline__ bool team_barrier(Team* t, TeamRun& r) {
     __shared__ uint32_t s_ok;
     __builtin_amdgcn_s_waitcnt(0);  // this wave's loads, stores and atomics have completed
@@ -223,7 +258,7 @@ __device__ __forceinline__ bool team_barrier(Team* t, TeamRun& r) {
         } else {
             uint32_t i = 0;
             while (shared_load(&t->gen) < r.gen)
-                if (++i >= kTeamSpins || shared_load(&t->err)) {
+                if (++i >= r.spins || shared_load(&t->err)) {
                     shared_store(&t->err, 1u);
                     ok = 0;
                     break;
@@ -531,12 +566,15 @@ void wait_slot(volatile unsigned long long* slot, hipStream_t s, const char* wha
 
 // Iterations kept in flight by drive_loop: EVQ_LAUNCH_DEPTH (1..32), default 3.
 uint64_t launch_depth();
+// Polls of a team's waits: EVQ_TEAM_SPINS, read once; default kTeamSpins.
+uint32_t team_spins();
 // EVQ_TRACE_LOOPS=1: drive_loop prints each iteration's published count to stderr.
 bool trace_loops();
 
 // Counts a published word in; true when it says the loop is done.
 inline bool loop_step(unsigned long long w, const char* what, uint64_t max_iters, uint64_t& consumed, uint64_t* items) {
-    const uint32_t n = (uint32_t)w, it = (uint32_t)(w >> 32) & 0x7FFFFFFFu;
+    if (w & kSlotFailed) fail(EVQ_EDEVICE, std::string(what) + ": a team of blocks gave up waiting for its members");
+    const uint32_t n = (uint32_t)w, it = (uint32_t)(w >> 32) & 0x3FFFFFFFu;
     if (trace_loops())
         fprintf(stderr, "[evq] %s iteration %llu: %u (%u iterations)\n", what, (unsigned long long)consumed, n, it);
     if (items) *items += n;

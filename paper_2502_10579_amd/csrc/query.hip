@@ -377,7 +377,7 @@ struct RelaxArgs {
     // A team's lists (k_relax_team): stamps over compact ids, its control block
     uint32_t* stamp;
     Team* team;
-    uint32_t place;
+    TeamRules rules;
     FrontierCounters* cnt;
     unsigned long long* stats;  // [1] edge visits, [2] lane relaxations, [3] seed edges
     uint32_t nU;
@@ -655,7 +655,9 @@ __global__ void __launch_bounds__(kBlock)
     constexpr int kStageRecs = kStageTasks * (int)kRelaxChunk;
     __shared__ uint32_t s_c[kStageTasks], s_e0[kStageTasks], s_ne[kStageTasks];
     __shared__ Rec<T::NLW> s_rec[kStageTasks][kRelaxChunk];
-    if (tag && r.team->ran == tag) return;  // a team ran this iteration and published
+    const TeamEnd fared = team_end(r.team, tag);
+    if (fared == TeamEnd::kGaveUp && blockIdx.x == 0 && threadIdx.x == 0) team_report(r.cnt, h, slot);
+    if (fared != TeamEnd::kNone) return;
     const int p = h ^ (int)uniform(r.cnt->flip[h]);
     const uint64_t* __restrict__ tasks = p ? tasks1 : tasks0;
     const unsigned long long cx = expand_prologue(r.cnt, h, p, slot);
@@ -895,7 +897,7 @@ __global__ void __launch_bounds__(kBlock)
     unsigned long long x = r.cnt->packed[p];
     if (items_of(x) == 0 || edges_of(x) > limit || epoch == 0) return;
     TeamRun team;
-    if (!team_join(r.team, r.place, team)) return;
+    if (!team_join(r.team, r.rules, epoch, team)) return;
     uint32_t k = 0, items = 0;
     int q = p;
     for (;;) {
@@ -1379,7 +1381,7 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     ra.tasks[1] = two ? ra.tasks[0] + max_tasks : ra.tasks[0];
     ra.stamp = f.stamp;
     ra.team = f.team;
-    ra.place = f.place;
+    ra.rules = f.rules;
     ra.cnt = f.cnt;
     ra.stats = f.stats;
     ra.nU = red.nU;

@@ -374,6 +374,11 @@ void set_tuning(const evq_tuning& t) {
 
 uint64_t launch_depth() { return tuning().launch_depth; }
 
+uint32_t team_spins() {
+    static const uint32_t n = env_u32("EVQ_TEAM_SPINS", kTeamSpins);
+    return n;
+}
+
 bool trace_loops() { return tuning().trace_loops != 0; }
 
 void wait_slot(volatile unsigned long long* slot, hipStream_t s, const char* what) {

@@ -78,7 +78,7 @@ struct SolveArgs {
     FrontierCounters* cnt;
     Team* team;
     uint32_t team_edges;  // a list of at most this many edges is left to a team (0: never)
-    uint32_t place;       // the team's eighth of the grid's blocks
+    TeamRules rules;
     unsigned long long* stats;
     uint32_t V;
     // pull step (full-window intersection only): reverse CSR and the share of
@@ -249,7 +249,7 @@ template <int A, int MODE, int MW, bool ST>
 __device__ __forceinline__ void team_iterations(const SolveArgs& a, const Mask<MW>& W, int h, int p,
                                                 unsigned long long x, uint32_t epoch, unsigned long long* slot) {
     TeamRun r;
-    if (!team_join(a.team, a.place, r)) return;
+    if (!team_join(a.team, a.rules, epoch, r)) return;
     uint32_t k = 0, items = 0;
     int q = p;
     for (;;) {
@@ -550,9 +550,12 @@ template <int A, int MODE, int MW, bool ST>
 __global__ void __launch_bounds__(kBlock)
     k_expand(SolveArgs a, Mask<MW> W, int h, uint32_t epoch, unsigned long long* slot) {
     constexpr int NW = kWalkers;
-    const bool ran = epoch && a.team->ran == epoch;  // a team ran this iteration and published
-    if (blockIdx.x == 0 && threadIdx.x == 0) team_reset(a.team);  // for the next compaction
-    if (ran) return;
+    const TeamEnd fared = team_end(a.team, epoch);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        team_reset(a.team);  // for the next compaction
+        if (fared == TeamEnd::kGaveUp) team_report(a.cnt, h, slot);
+    }
+    if (fared != TeamEnd::kNone) return;
     const int p = h ^ (int)uniform(a.cnt->flip[h]);
     const unsigned long long c0 = a.cnt->packed[p];
     bool pull = false;
@@ -713,7 +716,7 @@ __device__ __forceinline__ void start_counters(const SolveArgs& a, const StartAr
     c->flip[0] = c->flip[1] = 0u;
     c->status[0] = c->status[1] = 0u;
     team_reset(a.team);
-    a.team->ran = 0u;  // the tags may start again
+    a.team->began = a.team->ran = 0u;  // the tags may start again
     if (st.zero_stats)
         for (int i = 0; i < 8; ++i) a.stats[i] = 0ull;
     for (int i = 0; i < 4; ++i) st.aux[i] = 0ull;
@@ -839,7 +842,7 @@ SolveArgs make_args(const Graph& g, const Frontier& f, uint32_t* R) {
     a.cnt = f.cnt;
     a.team = f.team;
     a.team_edges = f.append_edges < kTeamEdges ? f.append_edges : kTeamEdges;
-    a.place = f.place;
+    a.rules = f.rules;
     a.stats = f.stats;
     a.V = g.V;
     a.rv_src = a.rv_w = a.rv_dst = a.rv_cnt = nullptr;
@@ -923,7 +926,7 @@ uint64_t dispatch_cup(uint32_t algo, const Graph& g, const Window& W, const uint
 __global__ void k_init_frontier(FrontierCounters* c, Team* team, unsigned long long* st, int n) {
     if (threadIdx.x == 0) {
         team_reset(team);
-        team->ran = 0u;
+        team->began = team->ran = 0u;
         c->packed[0] = c->packed[1] = 0ull;
         c->flip[0] = c->flip[1] = 0u;
         c->status[0] = c->status[1] = 0u;
@@ -968,7 +971,7 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
     }
     char* ctl = ws.buf<char>(Workspace::kControl, 512 + kTeamBytes);
     f.team = reinterpret_cast<Team*>(ctl + 512);
-    f.place = ws.place;
+    f.rules = {ws.place, team_spins()};
     f.cnt = reinterpret_cast<FrontierCounters*>(ctl);
     f.stats = reinterpret_cast<unsigned long long*>(ctl + 128);
     f.aux = reinterpret_cast<unsigned long long*>(ctl + 256);
