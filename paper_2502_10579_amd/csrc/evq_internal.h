@@ -185,7 +185,7 @@ class Workspace {
     uint64_t flags_clear = 0; // leading bytes of the flag buffer known to be clear between queries
     bool in_use = false;      // a query is running on it (a failed one leaves flags unknown)
     uint32_t epoch = 0;               // last epoch handed to an expansion (appending iterations)
-    uint32_t place = 0;               // which eighth of a grid's blocks forms this workspace's teams
+    uint32_t place = 0;               // which of every kTeamEvery blocks of a grid form this workspace's teams
     uint64_t stamps_known = 0;        // leading stamps that hold no epoch above it (the rest of the buffer is unset)
 
   private:

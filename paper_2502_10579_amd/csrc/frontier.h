@@ -110,21 +110,30 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
 //
 // What bounds a small iteration is latency: two launches of 2.4 us each and
 // their start and drain (10-12 us an iteration as launches, whatever its
-// size), against 1.3-1.7 us for a barrier over blocks that share an L2 and
-// about 2 us for the chain of dependent accesses of an expansion.  A query on
-// 4096 vertices and 8 snapshots went from 290 to 225 us with it, one on 2^18
-// vertices from 361 to 303; the batched loops, whose streams fill one
-// another's gaps, gained nothing (4.79 against 4.76 ms) and go without.
+// size), against 1.6-1.8 us for a barrier over 64 blocks and about 2 us for the
+// chain of dependent accesses of an expansion.  A query on 4096 vertices and 8
+// snapshots went from 290 to 225 us with it, one on 150001 vertices from 361 to
+// 303; the batched loops, whose streams fill one another's gaps, gained nothing
+// (4.79 against 4.76 ms) and go without.
 //
-// Members are the candidate blocks (every eighth block of the grid, which the
-// dispatcher places on one XCD) that are running when the first of them, after
-// a short wait, closes the registration; so every member is resident and the
-// barrier cannot wait for a block that has yet to start.  Blocks that come
-// later find the registration closed and leave.  Nothing depends on where the
-// members run: all they share goes through agent-scope relaxed atomic loads,
-// stores and read-modify-writes, and a member's accesses have completed
-// (s_waitcnt) before it arrives at the barrier.  An agent-scope fence would do
-// as well but writes the L2 back (7.6 us a barrier against 1.3).
+// Members are the candidate blocks (every kTeamEvery-th block of the grid) that
+// are running when the first of them, after a short wait, closes the
+// registration; so every member is resident and the barrier cannot wait for a
+// block that has yet to start.  Blocks that come later find the registration
+// closed and leave.  Nothing depends on where the members run: all they share
+// goes through agent-scope relaxed atomic loads, stores and read-modify-writes,
+// and a member's accesses have completed (s_waitcnt) before it arrives at the
+// barrier.  An agent-scope fence would do as well but writes the L2 back (7.6
+// us a barrier of 32 blocks against 1.3).
+//
+// The dispatcher deals consecutive blocks to the 8 XCDs in turn, so every
+// eighth block would put a team on one L2.  That buys next to nothing (64
+// blocks, a store per thread: 1.7 us a barrier, 1.8 from every 1st, 2nd or 4th
+// block) and takes a launch of 512 blocks, which callers on several streams pay
+// for.  Microseconds a query without teams, from every 8th, every 2nd and every
+// block: 4096 vertices, one caller 350, 267, 245, 250, eight callers 87, 101,
+// 68, 64; 150001 vertices 295, 236, 236, 242 and 103, 108, 98, 99; 2^20
+// vertices 995, 929, 929, 938 and 640, 675, 640, 636.
 //
 // Every wait is bounded.  A member whose wait runs out leaves, the others'
 // next wait runs out too, and the lists are then in no known state: the
@@ -148,6 +157,8 @@ struct Team {
     unsigned long long result;  // count of the list the team left
 };
 constexpr uint32_t kTeamBlocks = 64;
+constexpr uint32_t kTeamEvery = 2;
+constexpr uint32_t kTeamGrid = kTeamBlocks * kTeamEvery;  // blocks of a launch with room for a whole team
 constexpr uint32_t kTeamIters = 1024;      // most iterations of one launch
 constexpr uint32_t kTeamSpins = 1u << 24;  // polls of a wait (seconds); past them the member gives up
 constexpr uint64_t kTeamBytes = 1024;      // control bytes of a team
@@ -200,7 +211,7 @@ __device__ __forceinline__ void team_report(FrontierCounters* c, int h, unsigned
 
 // What the host lays down for teams.
 struct TeamRules {
-    uint32_t place;  // which eighth of a grid's blocks are the candidates
+    uint32_t place;  // which of every kTeamEvery blocks are the candidates
     uint32_t spins;  // polls of a wait before a member gives up
 };
 
@@ -211,19 +222,15 @@ struct TeamRun {
 // Every thread of a block calls it; true for the members' blocks.  tag (not
 // 0): this launch's.
 __device__ __forceinline__ bool team_join(Team* t, const TeamRules& rules, uint32_t tag, TeamRun& r) {
-    const uint32_t eighths = gridDim.x < 8u ? gridDim.x : 8u;
-    const uint32_t lane8 = rules.place % eighths;
-    if (blockIdx.x % 8u != lane8 || blockIdx.x / 8u >= kTeamBlocks) return false;
+    if (blockIdx.x % kTeamEvery != rules.place || blockIdx.x / kTeamEvery >= kTeamBlocks) return false;
     __shared__ uint32_t s_rank, s_n;
     if (threadIdx.x == 0) {
         uint32_t rank = kNone, n = 0;
         const uint32_t k = shared_load(&t->reg) >> 31 ? 1u << 31 : atomicAdd(&t->reg, 1u);
         if (!(k >> 31)) {
             rank = k;
-            const uint32_t want = (gridDim.x - lane8 + 7u) / 8u;
-            const uint32_t all = want < kTeamBlocks ? want : kTeamBlocks;
             if (k == 0) {
-                for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < all; ++i) __builtin_amdgcn_s_sleep(1);
+                for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < kTeamBlocks; ++i) __builtin_amdgcn_s_sleep(1);
                 n = atomicOr(&t->reg, 1u << 31);
                 t->began = tag;
                 shared_store(&t->n, n);

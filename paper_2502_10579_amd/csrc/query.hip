@@ -1426,7 +1426,7 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
         uint32_t epoch = 0;
         if (team_tasks) {
             epoch = take_epochs(f);
-            EVQ_LAUNCH("relax_team", (k_relax_team<A, (LG >= 8 ? LG : 8), ST>), 8 * kTeamBlocks, kBlock, s, ra, ra.cuo,
+            EVQ_LAUNCH("relax_team", (k_relax_team<A, (LG >= 8 ? LG : 8), ST>), kTeamGrid, kBlock, s, ra, ra.cuo,
                        ra.kc, ra.recs, p, team_tasks, epoch, slot);
         }
         if (staged == 2)

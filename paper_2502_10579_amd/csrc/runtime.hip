@@ -184,7 +184,7 @@ Workspace& Workspace::get(hipStream_t s) {
         if (kv.first.first == dev && kv.first.second == s) return *kv.second;
     all.push_back({{dev, s}, new Workspace(s)});
     static std::atomic<uint32_t> places{0};  // teams of concurrent streams gather on different XCDs
-    all.back().second->place = places.fetch_add(1, std::memory_order_relaxed) % 8;
+    all.back().second->place = places.fetch_add(1, std::memory_order_relaxed) % kTeamEvery;
     return *all.back().second;
 }
 

@@ -801,7 +801,7 @@ template <int A, int MODE, int MW, bool ST>
 uint64_t frontier_loop(SolveArgs a, const Mask<MW>& W, Frontier& f, hipStream_t s, uint64_t max_iters,
                        bool listed = false) {
     uint32_t cblocks = grid_for(a.V, kCompactIds, 4096);
-    if (a.team_edges && cblocks < 8 * kTeamBlocks) cblocks = 8 * kTeamBlocks;  // room for a whole team
+    if (a.team_edges && cblocks < kTeamGrid) cblocks = kTeamGrid;
     static const char* names[3] = {"solve_expand_cap_all", "solve_expand_cap", "solve_expand_cup"};
     auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         const uint32_t epoch = take_epochs(f);
