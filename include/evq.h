@@ -384,7 +384,9 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *                 (each improved vertex once, by a per-vertex stamp) instead
  *                 of marking flags for a compaction to scan (default 131072;
  *                 0: never).  Runs of iterations with at most this many edges,
- *                 and at most 32768, are done by one launch.
+ *                 and at most 32768 (2048 for each of the blocks that take
+ *                 part, where other streams leave fewer than 16), are done by
+ *                 one launch.
  *   append_items  EVQ_APPEND_ITEMS: ... likewise an iteration whose frontier
  *                 has at most this many vertices (default 0: never).
  *   relax_staged  EVQ_RELAX_STAGED: the multi-snapshot relaxation stages each
@@ -412,10 +414,11 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *                 the graph holds the map both ways on the device (8 bytes
  *                 per vertex) and on the host (4).  Read by evq_build; later
  *                 versions (evq_append) keep their graph's numbering.
- * The blocks that run small iterations together wait for one another at most
- * EVQ_TEAM_SPINS polls (environment only, read once; default 2^24, seconds);
- * a call in which such a wait runs out returns EVQ_EDEVICE and leaves no
- * answer, and later calls start afresh.
+ * The blocks that run small iterations together are at most EVQ_TEAM_BLOCKS
+ * (1..64, default 64) and wait for one another at most EVQ_TEAM_SPINS polls
+ * (default 2^24, seconds; both environment only, read once).  A call in which
+ * such a wait runs out returns EVQ_EDEVICE and leaves no answer; later calls
+ * start afresh.
  * evq_tuning_set: EVQ_EINVAL on NULL, launch_depth outside 1..32,
  * split_min == 0 or relax_staged not 0, 2 or 4; calls already running keep
  * the values they started with.

@@ -25,7 +25,7 @@ struct Frontier {
     uint32_t append_items = 0;   // ... or up to this many frontier vertices (0: never)
     FrontierCounters* cnt = nullptr;
     Team* team = nullptr;        // control block of the teams (frontier.h)
-    TeamRules rules{0, kTeamSpins};
+    TeamRules rules{0, kTeamSpins, kTeamBlocks};
     unsigned long long* stats = nullptr;  // [0] bound-solve edge visits, [1..] relaxer counters
     unsigned long long* aux = nullptr;    // 128 bytes of scratch counters for the reduction
     int p = 0;                            // parity of the next compaction (continues across phases)

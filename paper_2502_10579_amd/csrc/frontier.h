@@ -135,6 +135,15 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
 // 68, 64; 150001 vertices 295, 236, 236, 242 and 103, 108, 98, 99; 2^20
 // vertices 995, 929, 929, 938 and 640, 675, 640, 636.
 //
+// A team takes a list only if it is no more than kTeamRounds rounds of each
+// member (a tile of edges, or its lane groups' tasks), and hands a longer one
+// to the launches.  On an idle device all 64 candidates register, and the rule
+// changes nothing; where other streams fill it (the mid query from 2, 4 or 8
+// threads) teams of any size from one block up were counted, and without the
+// rule one block would run 64 tiles an iteration that a launch spreads over the
+// device.  1, 2, 4 and 64 rounds measured the same in those calls, so 4 bounds
+// the worst case at about what the two launches of an iteration cost.
+//
 // Every wait is bounded.  A member whose wait runs out leaves, the others'
 // next wait runs out too, and the lists are then in no known state: the
 // expansion's launch that follows finds the team begun and not ended
@@ -160,6 +169,7 @@ constexpr uint32_t kTeamBlocks = 64;
 constexpr uint32_t kTeamEvery = 2;
 constexpr uint32_t kTeamGrid = kTeamBlocks * kTeamEvery;  // blocks of a launch with room for a whole team
 constexpr uint32_t kTeamIters = 1024;      // most iterations of one launch
+constexpr uint32_t kTeamRounds = 4;        // most rounds of a member in an iteration
 constexpr uint32_t kTeamSpins = 1u << 24;  // polls of a wait (seconds); past them the member gives up
 constexpr uint64_t kTeamBytes = 1024;      // control bytes of a team
 static_assert(sizeof(Team) <= kTeamBytes, "team control block");
@@ -211,18 +221,22 @@ __device__ __forceinline__ void team_report(FrontierCounters* c, int h, unsigned
 
 // What the host lays down for teams.
 struct TeamRules {
-    uint32_t place;  // which of every kTeamEvery blocks are the candidates
-    uint32_t spins;  // polls of a wait before a member gives up
+    uint32_t place;   // which of every kTeamEvery blocks are the candidates
+    uint32_t spins;   // polls of a wait before a member gives up
+    uint32_t blocks;  // most members (at most kTeamBlocks)
 };
 
 struct TeamRun {
     uint32_t rank, n, gen, spins;
 };
 
-// Every thread of a block calls it; true for the members' blocks.  tag (not
-// 0): this launch's.
-__device__ __forceinline__ bool team_join(Team* t, const TeamRules& rules, uint32_t tag, TeamRun& r) {
-    if (blockIdx.x % kTeamEvery != rules.place || blockIdx.x / kTeamEvery >= kTeamBlocks) return false;
+// Every thread of a block calls it; true for the members' blocks, unless the
+// list's `work` is more than kTeamRounds rounds of `round` for each of them (then
+// they leave it to the launches; all see the same number).  tag (not 0): this
+// launch's.
+__device__ __forceinline__ bool team_join(Team* t, const TeamRules& rules, uint32_t work, uint32_t round, uint32_t tag,
+                                          TeamRun& r) {
+    if (blockIdx.x % kTeamEvery != rules.place || blockIdx.x / kTeamEvery >= rules.blocks) return false;
     __shared__ uint32_t s_rank, s_n;
     if (threadIdx.x == 0) {
         uint32_t rank = kNone, n = 0;
@@ -230,14 +244,15 @@ __device__ __forceinline__ bool team_join(Team* t, const TeamRules& rules, uint3
         if (!(k >> 31)) {
             rank = k;
             if (k == 0) {
-                for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < kTeamBlocks; ++i) __builtin_amdgcn_s_sleep(1);
+                for (uint32_t i = 0; i < 32u && shared_load(&t->reg) < rules.blocks; ++i) __builtin_amdgcn_s_sleep(1);
                 n = atomicOr(&t->reg, 1u << 31);
-                t->began = tag;
+                if (work <= n * kTeamRounds * round) t->began = tag;
                 shared_store(&t->n, n);
             } else {
                 for (uint32_t i = 0; i < rules.spins && n == 0; ++i) n = shared_load(&t->n);
                 if (n == 0) rank = kNone;
             }
+            if (work > n * kTeamRounds * round) rank = kNone;
         }
         s_rank = rank;
         s_n = n;
@@ -573,8 +588,9 @@ void wait_slot(volatile unsigned long long* slot, hipStream_t s, const char* wha
 
 // Iterations kept in flight by drive_loop: EVQ_LAUNCH_DEPTH (1..32), default 3.
 uint64_t launch_depth();
-// Polls of a team's waits: EVQ_TEAM_SPINS, read once; default kTeamSpins.
-uint32_t team_spins();
+// Polls of a team's waits (EVQ_TEAM_SPINS, default kTeamSpins) and its most
+// members (EVQ_TEAM_BLOCKS, default and at most kTeamBlocks), read once.
+TeamRules team_rules(uint32_t place);
 // EVQ_TRACE_LOOPS=1: drive_loop prints each iteration's published count to stderr.
 bool trace_loops();
 

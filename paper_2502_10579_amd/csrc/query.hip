@@ -892,12 +892,13 @@ __device__ __forceinline__ void team_relax(const RelaxArgs& r, const uint32_t* _
 template <int A, int LG, bool ST>
 __global__ void __launch_bounds__(kBlock)
     k_relax_team(RelaxArgs r, const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc,
-                 const void* __restrict__ recs, int h, uint32_t limit, uint32_t epoch, unsigned long long* slot) {
+                 const void* __restrict__ recs, int h, uint32_t round, uint32_t epoch, unsigned long long* slot) {
     const int p = h ^ (int)uniform(r.cnt->flip[h]);
     unsigned long long x = r.cnt->packed[p];
-    if (items_of(x) == 0 || edges_of(x) > limit || epoch == 0) return;
+    if (items_of(x) == 0 || edges_of(x) > kTeamBlocks * round || epoch == 0) return;
     TeamRun team;
-    if (!team_join(r.team, r.rules, epoch, team)) return;
+    if (!team_join(r.team, r.rules, edges_of(x), round, epoch, team)) return;
+    const uint32_t most = round * (team.n * kTeamRounds < kTeamBlocks ? team.n * kTeamRounds : kTeamBlocks);
     uint32_t k = 0, items = 0;
     int q = p;
     for (;;) {
@@ -908,7 +909,7 @@ __global__ void __launch_bounds__(kBlock)
         q ^= 1;
         if (!team_barrier(r.team, team)) return;
         x = shared_load(&r.team->packed[k % 3]);
-        if (x == 0 || edges_of(x) > limit || k == kTeamIters) break;
+        if (x == 0 || edges_of(x) > most || k == kTeamIters) break;
     }
     if (team.rank == 0 && threadIdx.x == 0) team_leave(r.cnt, r.team, epoch, h, q, x, items, k, slot);
 }
@@ -1415,7 +1416,7 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     const uint32_t sblocks = grid_for((uint64_t)red.nU + red.TU / kRelaxChunk,
                                       (kBlock / 64) * T::G * (staged ? staged : 1), EVQ_RELAX_BLOCKS);
     // iterations of at most one round of a team (2 tasks per lane group and member) go to it
-    const uint32_t team_tasks = staged && two ? kTeamBlocks * (kBlock / 64) * T::G * 2 : 0u;
+    const uint32_t team_tasks = staged && two ? (kBlock / 64) * T::G * 2 : 0u;
     auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         if (direct) {
             EVQ_LAUNCH("relax_compact", k_relax_compact<true>, cblocks, kCompactBlock, s, ra, p, first ? 1 : 0);

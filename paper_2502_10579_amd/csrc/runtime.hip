@@ -374,9 +374,10 @@ void set_tuning(const evq_tuning& t) {
 
 uint64_t launch_depth() { return tuning().launch_depth; }
 
-uint32_t team_spins() {
-    static const uint32_t n = env_u32("EVQ_TEAM_SPINS", kTeamSpins);
-    return n;
+TeamRules team_rules(uint32_t place) {
+    static const uint32_t spins = env_u32("EVQ_TEAM_SPINS", kTeamSpins);
+    static const uint32_t blocks = std::min(kTeamBlocks, std::max(1u, env_u32("EVQ_TEAM_BLOCKS", kTeamBlocks)));
+    return {place, spins, blocks};
 }
 
 bool trace_loops() { return tuning().trace_loops != 0; }

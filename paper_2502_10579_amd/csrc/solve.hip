@@ -243,13 +243,16 @@ __device__ __forceinline__ void team_step(const SolveArgs& a, const Mask<MW>& W,
 }
 
 // A team's launch: iterations from list p (count x) on, until the list is
-// empty, has more than team_edges edges (the launches take over again), or
+// empty, has more than team_edges edges or more than kTeamRounds tiles for each
+// member (the launches take over again, at the first list if that is one), or
 // kTeamIters have been run.  Epochs epoch .. epoch + kTeamIters - 1 are its own.
 template <int A, int MODE, int MW, bool ST>
 __device__ __forceinline__ void team_iterations(const SolveArgs& a, const Mask<MW>& W, int h, int p,
                                                 unsigned long long x, uint32_t epoch, unsigned long long* slot) {
     TeamRun r;
-    if (!team_join(a.team, a.rules, epoch, r)) return;
+    if (!team_join(a.team, a.rules, edges_of(x), kCompactBlock, epoch, r)) return;
+    const uint32_t all = r.n * kTeamRounds * kCompactBlock;
+    const uint32_t most = all < a.team_edges ? all : a.team_edges;
     uint32_t k = 0, items = 0;
     int q = p;
     for (;;) {
@@ -260,7 +263,7 @@ __device__ __forceinline__ void team_iterations(const SolveArgs& a, const Mask<M
         q ^= 1;
         if (!team_barrier(a.team, r)) return;
         x = shared_load(&a.team->packed[k % 3]);
-        if (x == 0 || edges_of(x) > a.team_edges || k == kTeamIters) break;
+        if (x == 0 || edges_of(x) > most || k == kTeamIters) break;
     }
     if (r.rank == 0 && threadIdx.x == 0) team_leave(a.cnt, a.team, epoch, h, q, x, items, k, slot);
 }
@@ -309,16 +312,12 @@ __global__ void __launch_bounds__(kCompactBlock)
             }
         }
     }
-    if (a.team_edges && epoch && (status & 6u) && c->delta == 0 && !lh) {
-        const unsigned long long x = (status & 4u) ? a.team->result : c->packed[p];
-        if (x && edges_of(x) <= a.team_edges) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) c->packed[p ^ 1] = 0ull;
-            team_iterations<A, MODE, MW, ST>(a, W, h, p, x, epoch, slot);
-            return;
-        }
-    }
     const bool skip = compaction_skips(c, p, status, a.team);
     if (lh && blockIdx.x == 0 && threadIdx.x == 0) c->bthr[p] = bt;
+    if (a.team_edges && epoch && (status & 6u) && c->delta == 0 && !lh) {
+        const unsigned long long x = (status & 4u) ? a.team->result : c->packed[p];
+        if (x && edges_of(x) <= a.team_edges) team_iterations<A, MODE, MW, ST>(a, W, h, p, x, epoch, slot);
+    }
     if (skip) return;
     const uint32_t thr = c->thr;
     const bool nf = c->delta != 0;
@@ -971,7 +970,7 @@ Frontier make_frontier(const Graph& g, Workspace& ws, hipStream_t s) {
     }
     char* ctl = ws.buf<char>(Workspace::kControl, 512 + kTeamBytes);
     f.team = reinterpret_cast<Team*>(ctl + 512);
-    f.rules = {ws.place, team_spins()};
+    f.rules = team_rules(ws.place);
     f.cnt = reinterpret_cast<FrontierCounters*>(ctl);
     f.stats = reinterpret_cast<unsigned long long*>(ctl + 128);
     f.aux = reinterpret_cast<unsigned long long*>(ctl + 256);
