@@ -77,7 +77,8 @@ struct SolveArgs {
     uint32_t append_items;  // ... or at most this many frontier vertices (0: never)
     FrontierCounters* cnt;
     Team* team;
-    uint32_t team_edges;  // a list of at most this many edges is left to a team (0: never)
+    uint32_t team_edges;  // a list of at most this many edges is left to a team (0: never, as in the
+                          // near/far and bucketed schedules, whose lists always come from a scan)
     TeamRules rules;
     unsigned long long* stats;
     uint32_t V;
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(kCompactBlock)
     }
     const bool skip = compaction_skips(c, p, status, a.team);
     if (lh && blockIdx.x == 0 && threadIdx.x == 0) c->bthr[p] = bt;
-    if (a.team_edges && epoch && (status & 6u) && c->delta == 0 && !lh) {
+    if (a.team_edges && epoch && (status & 6u)) {
         const unsigned long long x = (status & 4u) ? a.team->result : c->packed[p];
         if (x && edges_of(x) <= a.team_edges) team_iterations<A, MODE, MW, ST>(a, W, h, p, x, epoch, slot);
     }
@@ -864,6 +865,7 @@ uint64_t solve_cap_t(const Graph& g, const Window& W, uint32_t source, uint32_t*
         }
     }
     const uint32_t fd = bd ? 0u : f.delta;
+    if (fd || bd) a.team_edges = 0;
     // a guard against runaway loops: a bucket end takes an iteration of its own at most once per vertex
     const uint64_t cap = bd ? 4ull * g.V + 16 : (uint64_t)g.V + 2;
     const bool listed = !fd && !bd;
@@ -889,6 +891,7 @@ uint64_t solve_cap_t(const Graph& g, const Window& W, uint32_t source, uint32_t*
 template <int A, int MW, bool ST>
 uint64_t solve_cup_t(const Graph& g, const Window& W, const uint32_t* rcap, uint32_t* R, Frontier& f, hipStream_t s) {
     SolveArgs a = make_args(g, f, R);
+    if (f.delta) a.team_edges = 0;
     EVQ_LAUNCH("solve_start", k_cup_start, grid_for((g.V + 3) / 4, 256 * 4, 2048), 256, s, a,
                (StartArgs{f.delta, f.heavy, 0u, 0u, 0u, f.aux}), rcap);
     f.aux_clear = true;
