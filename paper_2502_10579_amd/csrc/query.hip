@@ -1375,9 +1375,13 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     ra.fo = f.fo;  // V entries each, free once the bound solves are done (nU <= V)
     ra.fv = f.fv;
     const uint64_t max_tasks = (uint64_t)red.nU + red.TU / kRelaxChunk + 64;
-    // a team lists tasks into a second buffer; a no-allocation call whose scratch holds one only does without
+    // the block stages its tasks in LDS, 2 or 4 per lane group (evq_tuning.relax_staged); the one-lane
+    // layout of the sequential ablation keeps the per-group kernel
+    const uint32_t staged = LG >= 8 ? tuning().relax_staged : 0u;
+    // a team, which the staged kernel alone has, lists tasks into a second buffer; a no-allocation call whose
+    // scratch holds one only does without
     const NoAlloc* na = noalloc_ctx();
-    const bool two = !na || na->used + 2 * max_tasks * 8 + 256 <= na->cap;
+    const bool two = staged && (!na || na->used + 2 * max_tasks * 8 + 256 <= na->cap);
     ra.tasks[0] = ws.buf<uint64_t>(Workspace::kTasks, (two ? 2 : 1) * max_tasks);
     ra.tasks[1] = two ? ra.tasks[0] + max_tasks : ra.tasks[0];
     ra.stamp = f.stamp;
@@ -1410,13 +1414,10 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     const uint32_t tblocks = grid_for(((uint64_t)red.nU + red.TU / kRelaxChunk + 63) / 64, kBlock / 64, 2048);
     const uint32_t rblocks =
         grid_for(((uint64_t)red.nU + red.TU / kRelaxChunk + T::G - 1) / T::G, kBlock / 64, EVQ_RELAX_BLOCKS);
-    // the block stages its tasks in LDS, 2 or 4 per lane group (evq_tuning.relax_staged); the one-lane
-    // layout of the sequential ablation keeps the per-group kernel
-    const uint32_t staged = LG >= 8 ? tuning().relax_staged : 0u;
     const uint32_t sblocks = grid_for((uint64_t)red.nU + red.TU / kRelaxChunk,
                                       (kBlock / 64) * T::G * (staged ? staged : 1), EVQ_RELAX_BLOCKS);
     // iterations of at most one round of a team (2 tasks per lane group and member) go to it
-    const uint32_t team_tasks = staged && two ? (kBlock / 64) * T::G * 2 : 0u;
+    const uint32_t team_tasks = two ? (kBlock / 64) * T::G * 2 : 0u;
     auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         if (direct) {
             EVQ_LAUNCH("relax_compact", k_relax_compact<true>, cblocks, kCompactBlock, s, ra, p, first ? 1 : 0);
