@@ -31,3 +31,19 @@ def test_first_bad_edge_is_named(where, at, field, value, msg):
     parts["adds"][149999, 0] = 5000  # a later one, in the last piece
     assert _build(evq, 1000, parts["base"], parts["dels"], parts["adds"]) == evq.EVQ_EINVAL
     assert msg in evq.last_error(), evq.last_error()
+
+
+@pytest.mark.parametrize("bad,msg", [(None, "batch deletions is NULL"), ("base", "base: zero weight at index 199999"),
+                                     ("adds", "batch deletions is NULL")])
+def test_null_span_is_named_in_its_turn(bad, msg):
+    import paper_2502_10579_amd as evq
+    parts = {k: np.ones((n, 3), np.uint32) for k, n in (("base", 200000), ("adds", 10))}
+    if bad:
+        parts[bad][-1, 2] = 0
+    arr = (evq.Batch * 1)()
+    ptr = lambda x: x.ctypes.data_as(ctypes.POINTER(evq.Edge))
+    arr[0] = evq.Batch(None, 7, ptr(parts["adds"]), 10)
+    h = ctypes.c_void_p()
+    rc = evq.lib.evq_build(1000, ptr(parts["base"]), len(parts["base"]), arr, 1, None, None, ctypes.byref(h))
+    assert rc == evq.EVQ_EINVAL and not h.value
+    assert msg in evq.last_error(), evq.last_error()
