@@ -5,6 +5,7 @@ each query runs on a fresh one, and the pool's bytes in use before and after it
 are what its workspace takes.
 """
 import ctypes
+import gc
 import threading
 
 import numpy as np
@@ -47,6 +48,7 @@ def test_one_task_buffer_without_teams(evq):
             for kind in ({}, {"sequential": True}):
                 def work():
                     with evq.tuning(relax_staged=staged):
+                        gc.collect()  # results of earlier tests that nothing holds any more
                         torch.cuda.synchronize()
                         before = _pool_bytes(evq)
                         got, st = gpu_values(g, oracle.SSSP, 1, 0, 8, stats=True, **kind)
@@ -58,5 +60,6 @@ def test_one_task_buffer_without_teams(evq):
                 t.start()
                 t.join()
     assert len(unstable) == 4 and min(unstable.values()) > 1000, unstable
-    assert took[0, 1] == took[2, 1], took
-    assert took[2, 0] - took[0, 0] >= 8 * unstable[2, 0], (took, unstable)  # the buffer holds 8 bytes per vertex, or more
+    buffer = 8 * unstable[2, 0]  # bytes it holds at least: 8 per vertex
+    assert took[2, 0] - took[0, 0] >= buffer, (took, unstable)
+    assert abs(took[2, 1] - took[0, 1]) < buffer, (took, unstable)
