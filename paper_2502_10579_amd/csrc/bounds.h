@@ -35,6 +35,7 @@ struct Frontier {
     bool fresh = true;                    // the counters and statistics have not been initialised yet
     bool aux_clear = false;               // aux is cleared for the next reduction
     uint64_t items = 0;                   // frontier items processed so far (published counts)
+    uint64_t reached = ~0ull;             // ... by the last intersection solve (its reach, or more; ~0: not known)
 };
 
 // Near/far step for a query: EVQ_DELTA overrides, else a per-algorithm default.

@@ -250,8 +250,8 @@ struct ReduceArgs {
     const uint32_t* rc;
     const uint32_t* ruo;
     const uint32_t* cid_of;
-    // The bounds of the window the values start from (null in the plain
-    // evaluation): an edge u -> v is kept only if the best value u can have in
+    // The bounds of the window the values start from (null: every edge between
+    // unstable vertices is kept): an edge u -> v is kept only if the best value u can have in
     // any snapshot (its union bound) carries over the edge to something better
     // than v's worst (its intersection bound).
     const uint32_t* rcap;
@@ -274,6 +274,12 @@ struct ReduceArgs {
 // (1M vertices, 64 snapshots, SSSP from a source whose first edges change: the
 // query 1.74 -> 1.31 ms, of it the relaxation 1.45 -> 0.5; 100k + 100k updates
 // per snapshot: 3.58 -> 3.00 ms.)
+// It costs a second gather for every edge that passes (8M vertices, 3.9M of
+// them unstable, 138M edges all kept: this kernel 2.60 -> 3.26 ms), 5% of what
+// the relaxation of an edge takes, and drops edges into vertices that the
+// intersection solve reached only: where it reached less than a thousandth of
+// the unstable ones (a source all of whose edges change) the bounds are left
+// out.
 template <int A, int MW, int NLW>
 __global__ void __launch_bounds__(kBlock) k_reduce(ReduceArgs a) {
     Rec<NLW>* __restrict__ out = static_cast<Rec<NLW>*>(a.recs);
@@ -1258,6 +1264,7 @@ struct Reduced {
     uint32_t* kc = nullptr;
     void* recs = nullptr;
     bool split = false;  // |U| exceeded the caller's threshold: no subgraph was built
+    bool filter = false; // edges that the bounds show to be useless are left out (k_reduce)
 };
 
 void reduce_edges(const Graph& g, uint32_t algo, Reduced& r, const Window& W, uint32_t NLW, const uint32_t* rcap,
@@ -1305,8 +1312,8 @@ Reduced reduce_graph(const Graph& g, uint32_t algo, const uint32_t* rcap, const 
         r.split = true;
         return r;
     }
-    reduce_edges(g, algo, r, W, NLW, all_vertices ? nullptr : rcap, all_vertices ? nullptr : rcup, ws,
-                 s);  // kc starts at zero (k_unstable)
+    r.filter = !all_vertices && f.reached >= r.nU / 1024;
+    reduce_edges(g, algo, r, W, NLW, rcap, rcup, ws, s);  // kc starts at zero (k_unstable)
     return r;
 }
 
@@ -1318,7 +1325,7 @@ void launch_reduce(const Graph& g, uint32_t NLW, uint32_t blocks, const ReduceAr
 }
 
 // The reduced subgraph's records for window W over the unstable set of r (kc
-// must start at zero); rcap, rcup: the bounds its values start from, or null.
+// must start at zero); rcap, rcup: the bounds its values start from.
 void reduce_edges(const Graph& g, uint32_t algo, Reduced& r, const Window& W, uint32_t NLW, const uint32_t* rcap,
                   const uint32_t* rcup, Workspace& ws, hipStream_t s) {
     r.recs = ws.raw(Workspace::kRecs, (r.TU + 1) * (NLW == 1 ? sizeof(Rec<1>) : sizeof(Rec<2>)));
@@ -1333,8 +1340,8 @@ void reduce_edges(const Graph& g, uint32_t algo, Reduced& r, const Window& W, ui
         a.rc = r.rc;
         a.ruo = r.ruo;
         a.cid_of = r.cid_of;
-        a.rcap = rcap;
-        a.rcup = rcup;
+        a.rcap = r.filter ? rcap : nullptr;
+        a.rcup = r.filter ? rcup : nullptr;
         a.kc = r.kc;
         a.recs = r.recs;
         a.nR = r.nR;
@@ -1532,7 +1539,9 @@ namespace {
 void bounds_impl(const Graph& g, uint32_t algo, uint32_t source, const Window& W, uint32_t* rcap, uint32_t* rcup,
                  Frontier& f, QueryOut& qo, hipStream_t s, Timer& tm) {
     const bool st = qo.want_stats;
+    const uint64_t items_before = f.items;
     qo.st.iters_cap = solve_cap(g, algo, W, source, rcap, f, s, st);
+    f.reached = f.items - items_before;
     tm.mark();
     if (st) {
         qo.st.edges_cap = read_stat(f.stats, 0, s);
