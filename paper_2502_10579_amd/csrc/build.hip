@@ -558,12 +558,17 @@ void append_impl(const Graph& old, Graph* g, const uint32_t* d_ev, uint64_t n_de
 // whether it stays, whether it moves.  Only the words' stayer counts are
 // scanned; an edge's rank is its word's scanned count plus a population
 // count.  The bound is HBM: the masks once, then every array in and out once.
-//   70M edges, 4M vertices, two-word masks, 20k + 20k updates: 11.7 -> 2.1 ms
-//   a call, placement 0.84 ms for 3.4 GB (4.0 TB/s), classes 0.29 ms for
-//   1.1 GB.  Before, each edge's source came from device atomics on the row
-//   starts (8.5 ms: the vertices without edges share their starts with others,
-//   and same-address atomics serialise) and an E-long scan, the ranks from two
-//   more such scans (0.95 ms in all), and each edge kept a byte of class.
+//   70M edges, 4M vertices, two-word masks, 20k + 20k updates: placement 0.84
+//   ms for 3.4 GB (4.0 TB/s), classes 0.29 ms for 1.1 GB; an append in a stream
+//   of them, each followed by a query, 11.7 -> 2.1 ms.  Before, each edge's
+//   source came from device atomics on the row starts and an E-long scan, the
+//   ranks from two more such scans (0.95 ms in all), and each edge kept a byte
+//   of class.  The atomics took 8.5 ms from the second append on: the vertices
+//   without edges, which the numbering puts last, share the row start of the
+//   next vertex with edges as soon as an appended edge leaves from one of them,
+//   and same-address atomics serialise; in a built graph they all start at E
+//   and were skipped.  Appends alone, the device waited for before and after
+//   each: the first 8.3 -> 8.1 ms, the second and later 17.3 -> 7.4.
 
 template <typename KT>
 __global__ void k_ev_keys(const uint32_t* __restrict__ ev, uint64_t n_del, uint64_t n_ev, KeyLayout L,

@@ -104,17 +104,17 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
     return x;
 }
 
-// A team: up to kTeamBlocks blocks of one expansion launch that run a loop's
-// small iterations themselves, with a barrier of their own between iterations
-// instead of a kernel boundary.
+// A team: up to kTeamBlocks blocks of one launch (the bound solves' compaction,
+// or the relaxation's k_relax_team) that run a loop's small iterations
+// themselves, with a barrier of their own between iterations instead of a
+// kernel boundary.
 //
 // What bounds a small iteration is latency: two launches of 2.4 us each and
 // their start and drain (10-12 us an iteration as launches, whatever its
 // size), against 1.6-1.8 us for a barrier over 64 blocks and about 2 us for the
-// chain of dependent accesses of an expansion.  A query on 4096 vertices and 8
-// snapshots went from 290 to 225 us with it, one on 150001 vertices from 361 to
-// 303; the batched loops, whose streams fill one another's gaps, gained nothing
-// (4.79 against 4.76 ms) and go without.
+// chain of dependent accesses of an expansion.  The batched loops, whose
+// streams fill one another's gaps, gained nothing (4.79 against 4.76 ms) and go
+// without; single queries' figures are below.
 //
 // Members are the candidate blocks (every kTeamEvery-th block of the grid) that
 // are running when the first of them, after a short wait, closes the

@@ -796,7 +796,7 @@ __global__ void __launch_bounds__(kBlock) k_seed_partial(SolveArgs a, Mask<MW> W
     }
 }
 
-// listed: the first frontier is in the item set already (k_solve_start).
+// listed: the first frontier is in the item set already (k_cap_start).
 template <int A, int MODE, int MW, bool ST>
 uint64_t frontier_loop(SolveArgs a, const Mask<MW>& W, Frontier& f, hipStream_t s, uint64_t max_iters,
                        bool listed = false) {
