@@ -363,7 +363,8 @@ evq_status evq_batch_config_set(const evq_batch_config* c);
  *   launch_depth  EVQ_LAUNCH_DEPTH: frontier iterations kept in flight, 1..32
  *                 (default 3).  Loops whose small iterations run many to a
  *                 launch (see append_edges; never one that defers vertices)
- *                 keep one in flight.
+ *                 keep one in flight until 16 launches in a row have run one
+ *                 iteration each.
  *   direct_tasks  EVQ_DIRECT_TASKS: reduced subgraphs of at most this many
  *                 relaxation tasks have them written by the frontier
  *                 compaction, larger ones by a kernel of their own (default

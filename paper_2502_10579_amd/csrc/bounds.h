@@ -67,7 +67,7 @@ inline uint32_t take_epochs(Frontier& f) {
     return e;
 }
 
-// Launches kept in flight when teams run the small iterations: a team
+// Launches kept in flight at first when teams run the small iterations: a team
 // publishes at its end, usually that the loop is done, and launches issued
 // before that is known cost 9 us; a large iteration publishes at its start and
 // hides the next one's launches.

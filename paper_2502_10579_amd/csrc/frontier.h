@@ -575,9 +575,9 @@ class HostSlots {
     unsigned long long* d_ = nullptr;
 };
 
-// Issues launches of an iteration (issue(it, parity, first)) `depth` ahead of
-// the one whose published word it waits for; stops at the first that says the
-// loop is done.  Returns the number of non-empty iterations and adds the
+// Issues launches of an iteration (issue(it, parity, first)) ahead of the one
+// whose published word it waits for (InFlight(depth) says how many); stops at
+// the first that says the loop is done.  Returns the number of non-empty iterations and adds the
 // published counts (items processed) to *items; f_parity is advanced past
 // every issued launch.
 template <typename IssueFn>
@@ -594,10 +594,33 @@ TeamRules team_rules(uint32_t place);
 // EVQ_TRACE_LOOPS=1: drive_loop prints each iteration's published count to stderr.
 bool trace_loops();
 
+// Iterations a launch ran, from its published word.
+inline uint32_t iterations_of(unsigned long long w) { return (uint32_t)(w >> 32) & 0x3FFFFFFFu; }
+
+// Launches a loop keeps in flight: launch_depth(), or the given depth where
+// teams run the small iterations.  Such a loop goes to launch_depth() once
+// kSteadyLaunches in a row have run one iteration each, and back with the next
+// that runs more: a deep graph whose lists stay above the teams' limit has
+// hundreds of such launches, where the next one's launch latency shows (BFS, 40000
+// to 480000 edges a list, 100 to 400 iterations: 3-10% of the query), while the
+// dense iterations of a power-law graph are fewer than that.
+class InFlight {
+  public:
+    explicit InFlight(uint64_t depth) : few_(depth ? depth : launch_depth()), most_(depth ? launch_depth() : few_) {
+        if (most_ < few_) most_ = few_;
+    }
+    uint64_t launches() const { return steady_ < kSteadyLaunches ? few_ : most_; }
+    void took(unsigned long long w) { steady_ = iterations_of(w) == 1 ? steady_ + 1 : 0; }
+
+  private:
+    static constexpr uint64_t kSteadyLaunches = 16;
+    uint64_t few_, most_, steady_ = 0;
+};
+
 // Counts a published word in; true when it says the loop is done.
 inline bool loop_step(unsigned long long w, const char* what, uint64_t max_iters, uint64_t& consumed, uint64_t* items) {
     if (w & kSlotFailed) fail(EVQ_EDEVICE, std::string(what) + ": a team of blocks gave up waiting for its members");
-    const uint32_t n = (uint32_t)w, it = (uint32_t)(w >> 32) & 0x3FFFFFFFu;
+    const uint32_t n = (uint32_t)w, it = iterations_of(w);
     if (trace_loops())
         fprintf(stderr, "[evq] %s iteration %llu: %u (%u iterations)\n", what, (unsigned long long)consumed, n, it);
     if (items) *items += n;
@@ -607,17 +630,19 @@ inline bool loop_step(unsigned long long w, const char* what, uint64_t max_iters
 }
 
 // Inside a no-allocation call: the published words go to the first bytes of
-// the scratch array; each batch of depth + 1 launches is followed
-// by one copy of its counts to host memory and a stream synchronisation.
+// the scratch array; each batch of launches (one more than in flight
+// otherwise) is followed by one copy of its counts to host memory and a stream
+// synchronisation.
 template <typename IssueFn>
 uint64_t drive_loop_sync(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_iters, const char* what,
                          uint64_t* items, uint64_t depth, NoAlloc& na) {
     static_assert(kNoAllocSlotBytes >= 33 * 8, "slots of one batch");
     unsigned long long* dslots = reinterpret_cast<unsigned long long*>(na.base);
-    const uint64_t batch = (depth ? depth : launch_depth()) + 1;
+    InFlight flight(depth);
     unsigned long long h[33];
     uint64_t issued = 0, consumed = 0;
     for (;;) {
+        const uint64_t batch = flight.launches() + 1;
         for (uint64_t j = 0; j < batch; ++j, ++issued) {
             issue(issued, f_parity, issued == 0, dslots + j);
             f_parity ^= 1;
@@ -626,6 +651,7 @@ uint64_t drive_loop_sync(IssueFn issue, int& f_parity, hipStream_t s, uint64_t m
         EVQ_HIP(hipStreamSynchronize(s));
         for (uint64_t j = 0; j < batch; ++j) {
             if (loop_step(h[j], what, max_iters, consumed, items)) return consumed;
+            flight.took(h[j]);
         }
     }
 }
@@ -634,7 +660,7 @@ template <typename IssueFn>
 uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_iters, const char* what,
                     uint64_t* items, uint64_t depth) {
     if (NoAlloc* na = noalloc_ctx()) return drive_loop_sync(issue, f_parity, s, max_iters, what, items, depth, *na);
-    const uint64_t kDepth = depth ? depth : launch_depth();
+    InFlight flight(depth);
     HostSlots& hs = HostSlots::get();
     uint64_t issued = 0, taken = 0, consumed = 0;
     const uint64_t base = hs.next;
@@ -646,7 +672,7 @@ uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_it
     uint64_t end = base;
     Advance adv{hs, end};
     for (;;) {
-        while (issued < taken + kDepth) {
+        while (issued < taken + flight.launches()) {
             const uint32_t k = (uint32_t)((base + issued) % HostSlots::kSlots);
             __atomic_store_n(&hs.host()[k], HostSlots::kEmpty, __ATOMIC_RELEASE);
             issue(issued, f_parity, issued == 0, hs.dev() + k);
@@ -657,7 +683,9 @@ uint64_t drive_loop(IssueFn issue, int& f_parity, hipStream_t s, uint64_t max_it
         volatile unsigned long long* slot = hs.host() + ((base + taken) % HostSlots::kSlots);
         wait_slot(slot, s, what);
         ++taken;
-        if (loop_step(*slot, what, max_iters, consumed, items)) break;
+        const unsigned long long w = *slot;
+        if (loop_step(w, what, max_iters, consumed, items)) break;
+        flight.took(w);
     }
     return consumed;
 }

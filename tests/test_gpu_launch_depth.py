@@ -43,3 +43,30 @@ def test_launches_in_flight(evq, schedule, cup, depth):
             assert cap == st["iters_cap"] + depth, (cap, st["iters_cap"])
             if cup:
                 assert launches["solve_expand_cup"] == st["iters_cup"] + depth, (launches, st["iters_cup"])
+
+
+@pytest.mark.parametrize("depth", [1, 3, 6])
+@pytest.mark.parametrize("layers,steady", [(12, False), (24, True)])
+def test_launches_in_flight_above_the_teams_limit(evq, layers, steady, depth):
+    """Layers of 8200 vertices and 32800 edges: every list but the source's goes to the launches."""
+    n, d, K = 8200, 4, 2
+    src, j = np.repeat(np.arange(n), d), np.tile(np.arange(d), n)
+    rows = [np.stack([np.zeros(n, np.int64), 1 + np.arange(n), np.full(n, 2)], 1)]
+    rows += [np.stack([1 + i * n + src, 1 + (i + 1) * n + (src + 977 * j) % n, 1 + j], 1) for i in range(layers)]
+    base = np.concatenate(rows).astype(np.uint32)
+    extra = [np.array([[5, 6, 9 + k]], np.uint32) for k in range(K)]
+    inst = synth.Instance(1 + (layers + 1) * n, base, [extra[0][:0]] * K, extra)
+    want = oracle.window_values(inst, oracle.BFS, 0, 0, K)
+    with evq.Graph.from_instance(inst) as g, evq.tuning(launch_depth=depth):
+        evq.timing_enable(True)
+        evq.timing_reset()
+        try:
+            got, st = gpu_values(g, oracle.BFS, 0, 0, K, stats=True)
+            launches = {k: n for k, (n, ms) in evq.timing_report().items()}
+        finally:
+            evq.timing_enable(False)
+        assert_equal_values(got, want, f"layers={layers} depth={depth}")
+        assert st["iters_cap"] == layers + 1  # the last layer has no edges
+        assert launches["solve_expand_cap_all"] == st["iters_cap"] + (depth if steady else 1), (launches, st)
+        out = evq.to_u32(g.query_noalloc(oracle.BFS, 0, 0, K)).reshape(want.shape)
+        assert_equal_values(out, want, f"layers={layers} depth={depth} without allocation")
