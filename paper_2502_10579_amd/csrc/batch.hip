@@ -111,7 +111,8 @@ __device__ __forceinline__ bool lane_has(const uint64_t* __restrict__ mask, uint
 // K = 64: 4.82 -> 4.66 ms; a burst of 12 on V = 2^18, E = 2^22 unchanged.
 template <int A, bool CUP, int MW, int CH, int NL>
 __global__ void __launch_bounds__(kBlock) k_bexpand(BatchArgs a, int p, unsigned long long* slot) {
-    const unsigned long long cx = expand_prologue(a.cnt, p, p, slot);
+    const unsigned long long cx = a.cnt->packed[p];
+    expand_prologue(a.cnt, p, p, cx, slot);
     const uint32_t n = edges_of(cx);  // tasks (the items are their vertices)
     if (n == 0) return;
     const uint32_t LQ = a.LQ;

@@ -69,7 +69,17 @@ __device__ __forceinline__ void mark(uint8_t* __restrict__ flags, uint32_t v) { 
 // Bytes of the flag array for n ids (a multiple of the 8 ids a lane reads).
 inline uint64_t flag_bytes(uint64_t n) { return (n + 7) & ~uint64_t(7); }
 
-// Expansion prologue: read this iteration's counts (of item parity p), tell the
+// Item parity and count of the iteration of host parity h.  Both counts are
+// read beside the flip, not after it: a kernel that calls this before its first
+// store waits for one access, and takes the values through the scalar cache.
+__device__ __forceinline__ unsigned long long read_list(const FrontierCounters* c, int h, int& p) {
+    const uint32_t f = c->flip[h];
+    const unsigned long long x0 = c->packed[0], x1 = c->packed[1];
+    p = h ^ (int)uniform(f);
+    return p ? x1 : x0;
+}
+
+// Expansion prologue (count x of item parity p, from read_list): tell the
 // next compaction (host parity h ^ 1) whether there was work and whether this
 // expansion appends the next list itself (`appends`, the same on every block),
 // publish the item count to the host slot.
@@ -79,9 +89,8 @@ inline uint64_t flag_bytes(uint64_t n) { return (n + 7) & ~uint64_t(7); }
 // frontier: it rises to the smallest key of this iteration's ids plus delta,
 // so a heavy id is expanded once its value is within delta of the best one
 // still moving (and, with positive steps, close to final).
-__device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* c, int h, int p,
-                                                              unsigned long long* slot, bool appends = false) {
-    const unsigned long long x = c->packed[p];
+__device__ __forceinline__ void expand_prologue(FrontierCounters* c, int h, int p, unsigned long long x,
+                                                unsigned long long* slot, bool appends = false) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         const uint32_t f = c->far[p];
         uint64_t t = c->thr;
@@ -101,7 +110,6 @@ __device__ __forceinline__ unsigned long long expand_prologue(FrontierCounters* 
         const uint32_t n = items_of(x) + f;
         __hip_atomic_store(slot, slot_word(n, n ? 1u : 0u, n == 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    return x;
 }
 
 // A team: up to kTeamBlocks blocks of one launch (the bound solves' compaction,
@@ -207,8 +215,9 @@ __device__ __forceinline__ void team_leave(FrontierCounters* c, Team* t, uint32_
 // or it began and did not end.
 enum class TeamEnd { kNone, kRan, kGaveUp };
 __device__ __forceinline__ TeamEnd team_end(const Team* t, uint32_t tag) {
-    if (tag == 0 || t->began != tag) return TeamEnd::kNone;
-    return t->ran == tag ? TeamEnd::kRan : TeamEnd::kGaveUp;
+    const uint32_t began = t->began, ran = t->ran;
+    if (tag == 0 || began != tag) return TeamEnd::kNone;
+    return ran == tag ? TeamEnd::kRan : TeamEnd::kGaveUp;
 }
 
 // The launch at host parity h found that the team before it gave up; one

@@ -442,9 +442,9 @@ __global__ void __launch_bounds__(kCompactBlock) k_relax_compact(RelaxArgs r, in
 
 // Frontier items of this iteration -> its tasks (write_tasks), unless a team left them.
 __global__ void __launch_bounds__(kBlock) k_relax_tasks(RelaxArgs r, int h, int first) {
+    int p;
+    const unsigned long long cx = read_list(r.cnt, h, p);
     if (!first && (r.cnt->status[h] & 4u)) return;
-    const int p = h ^ (int)uniform(r.cnt->flip[h]);
-    const unsigned long long cx = r.cnt->packed[p];
     write_tasks(r.fo, r.fv, items_of(cx), edges_of(cx), r.tasks[p]);
 }
 
@@ -569,9 +569,10 @@ __global__ void __launch_bounds__(kBlock)
             const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc, const void* __restrict__ recs_v, int h,
             unsigned long long* slot) {
     using T = Lanes<LG>;
-    const int p = h ^ (int)uniform(r.cnt->flip[h]);
+    int p;
+    const unsigned long long cx = read_list(r.cnt, h, p);
     const uint64_t* __restrict__ tasks = p ? tasks1 : tasks0;
-    const unsigned long long cx = expand_prologue(r.cnt, h, p, slot);
+    expand_prologue(r.cnt, h, p, cx, slot);
     const uint32_t n = edges_of(cx);  // tasks (the items are their vertices)
     if (n == 0) return;
     const Rec<T::NLW>* __restrict__ recs = static_cast<const Rec<T::NLW>*>(recs_v);
@@ -661,12 +662,13 @@ __global__ void __launch_bounds__(kBlock)
     constexpr int kStageRecs = kStageTasks * (int)kRelaxChunk;
     __shared__ uint32_t s_c[kStageTasks], s_e0[kStageTasks], s_ne[kStageTasks];
     __shared__ Rec<T::NLW> s_rec[kStageTasks][kRelaxChunk];
+    int p;
+    const unsigned long long cx = read_list(r.cnt, h, p);
     const TeamEnd fared = team_end(r.team, tag);
     if (fared == TeamEnd::kGaveUp && blockIdx.x == 0 && threadIdx.x == 0) team_report(r.cnt, h, slot);
     if (fared != TeamEnd::kNone) return;
-    const int p = h ^ (int)uniform(r.cnt->flip[h]);
     const uint64_t* __restrict__ tasks = p ? tasks1 : tasks0;
-    const unsigned long long cx = expand_prologue(r.cnt, h, p, slot);
+    expand_prologue(r.cnt, h, p, cx, slot);
     const uint32_t n = edges_of(cx);  // tasks
     if (n == 0) return;
     const Rec<T::NLW>* __restrict__ recs = static_cast<const Rec<T::NLW>*>(recs_v);
@@ -899,8 +901,8 @@ template <int A, int LG, bool ST>
 __global__ void __launch_bounds__(kBlock)
     k_relax_team(RelaxArgs r, const uint32_t* __restrict__ cuo, const uint32_t* __restrict__ kc,
                  const void* __restrict__ recs, int h, uint32_t round, uint32_t epoch, unsigned long long* slot) {
-    const int p = h ^ (int)uniform(r.cnt->flip[h]);
-    unsigned long long x = r.cnt->packed[p];
+    int p;
+    unsigned long long x = read_list(r.cnt, h, p);
     if (items_of(x) == 0 || edges_of(x) > kTeamBlocks * round || epoch == 0) return;
     TeamRun team;
     if (!team_join(r.team, r.rules, edges_of(x), round, epoch, team)) return;

@@ -297,7 +297,8 @@ template <int A, int MODE, int MW, bool ST>
 __global__ void __launch_bounds__(kCompactBlock)
     k_compact_frontier(SolveArgs a, Mask<MW> W, int h, uint32_t first, uint32_t epoch, unsigned long long* slot) {
     FrontierCounters* const c = a.cnt;
-    const int p = h ^ (int)uniform(c->flip[h]);
+    int p;
+    const unsigned long long listed = read_list(c, h, p), left = a.team->result;
     const uint32_t status = first ? first : c->status[h];
     const bool lh = a.nheavy != nullptr;
     uint32_t bt = 0xFFFFFFFFu;  // bucket bound: light edges of flagged vertices below it are expanded
@@ -316,7 +317,7 @@ __global__ void __launch_bounds__(kCompactBlock)
     const bool skip = compaction_skips(c, p, status, a.team);
     if (lh && blockIdx.x == 0 && threadIdx.x == 0) c->bthr[p] = bt;
     if (a.team_edges && epoch && (status & 6u)) {
-        const unsigned long long x = (status & 4u) ? a.team->result : c->packed[p];
+        const unsigned long long x = (status & 4u) ? left : listed;
         if (x && edges_of(x) <= a.team_edges) team_iterations<A, MODE, MW, ST>(a, W, h, p, x, epoch, slot);
     }
     if (skip) return;
@@ -550,25 +551,23 @@ template <int A, int MODE, int MW, bool ST>
 __global__ void __launch_bounds__(kBlock)
     k_expand(SolveArgs a, Mask<MW> W, int h, uint32_t epoch, unsigned long long* slot) {
     constexpr int NW = kWalkers;
+    int p;
+    const unsigned long long cx = read_list(a.cnt, h, p);
     const TeamEnd fared = team_end(a.team, epoch);
+    const uint32_t delta = a.cnt->delta;
+    const uint32_t n_in = MODE == 0 && a.pull_frac != kNone ? a.rv_cnt[1] : 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         team_reset(a.team);  // for the next compaction
         if (fared == TeamEnd::kGaveUp) team_report(a.cnt, h, slot);
     }
     if (fared != TeamEnd::kNone) return;
-    const int p = h ^ (int)uniform(a.cnt->flip[h]);
-    const unsigned long long c0 = a.cnt->packed[p];
-    bool pull = false;
-    if (MODE == 0 && a.pull_frac != kNone) {
-        const uint32_t n_in = a.rv_cnt[1];
-        pull = n_in && (uint64_t)edges_of(c0) * 1024u >= (uint64_t)n_in * a.pull_frac;
-    }
+    const bool pull = n_in && (uint64_t)edges_of(cx) * 1024u >= (uint64_t)n_in * a.pull_frac;
     // a sparse iteration (and no near/far schedule) lists the next frontier itself
-    const bool small = (a.append_edges && edges_of(c0) <= a.append_edges) ||
-                       (a.append_items && items_of(c0) <= a.append_items);
+    const bool small = (a.append_edges && edges_of(cx) <= a.append_edges) ||
+                       (a.append_items && items_of(cx) <= a.append_items);
     const bool lh = a.nheavy != nullptr;
-    const bool appends = !pull && small && a.cnt->delta == 0 && !lh && epoch != 0;
-    const unsigned long long cx = expand_prologue(a.cnt, h, p, slot, appends);
+    const bool appends = !pull && small && delta == 0 && !lh && epoch != 0;
+    expand_prologue(a.cnt, h, p, cx, slot, appends);
     const uint32_t n = items_of(cx), T = edges_of(cx);
     if (T == 0) return;
     if (pull) {
