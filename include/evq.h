@@ -127,7 +127,8 @@ typedef struct {
     double ms_total, ms_cap, ms_cup, ms_compact, ms_relax, ms_writeback;
     uint64_t n_unstable;        /* vertices whose intersection and union bounds differ */
     uint64_t n_seed_edges;      /* window-partial edges into unstable vertices (the reduced batches) */
-    uint64_t n_relax_edges;     /* reduced-subgraph edges: between unstable vertices, and by the bounds able to improve */
+    uint64_t n_relax_edges;     /* reduced-subgraph edges: between unstable vertices, less those that the bounds,
+                                   where they are read, show to be useless */
     uint64_t iters_cap, iters_cup, iters_relax;
     uint64_t edges_cap, edges_cup;        /* edge visits of the two bound solves */
     uint64_t edge_visits_relax;           /* edge visits of the multi-snapshot relaxation */
