@@ -215,8 +215,9 @@ __device__ __forceinline__ void team_leave(FrontierCounters* c, Team* t, uint32_
 // or it began and did not end.
 enum class TeamEnd { kNone, kRan, kGaveUp };
 __device__ __forceinline__ TeamEnd team_end(const Team* t, uint32_t tag) {
+    if (tag == 0) return TeamEnd::kNone;
     const uint32_t began = t->began, ran = t->ran;
-    if (tag == 0 || began != tag) return TeamEnd::kNone;
+    if (began != tag) return TeamEnd::kNone;
     return ran == tag ? TeamEnd::kRan : TeamEnd::kGaveUp;
 }
 

@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(kCompactBlock)
     k_compact_frontier(SolveArgs a, Mask<MW> W, int h, uint32_t first, uint32_t epoch, unsigned long long* slot) {
     FrontierCounters* const c = a.cnt;
     int p;
-    const unsigned long long listed = read_list(c, h, p), left = a.team->result;
+    const unsigned long long listed = read_list(c, h, p), left = a.team_edges ? a.team->result : 0ull;
     const uint32_t status = first ? first : c->status[h];
     const bool lh = a.nheavy != nullptr;
     uint32_t bt = 0xFFFFFFFFu;  // bucket bound: light edges of flagged vertices below it are expanded
@@ -553,10 +553,10 @@ __global__ void __launch_bounds__(kBlock)
     constexpr int NW = kWalkers;
     int p;
     const unsigned long long cx = read_list(a.cnt, h, p);
-    const TeamEnd fared = team_end(a.team, epoch);
+    const TeamEnd fared = team_end(a.team, a.team_edges ? epoch : 0u);
     const uint32_t delta = a.cnt->delta;
     const uint32_t n_in = MODE == 0 && a.pull_frac != kNone ? a.rv_cnt[1] : 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.team_edges && blockIdx.x == 0 && threadIdx.x == 0) {
         team_reset(a.team);  // for the next compaction
         if (fared == TeamEnd::kGaveUp) team_report(a.cnt, h, slot);
     }
