@@ -1387,10 +1387,15 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
     // the block stages its tasks in LDS, 2 or 4 per lane group (evq_tuning.relax_staged); the one-lane
     // layout of the sequential ablation keeps the per-group kernel
     const uint32_t staged = LG >= 8 ? tuning().relax_staged : 0u;
-    // a team, which the staged kernel alone has, lists tasks into a second buffer; a no-allocation call whose
-    // scratch holds one only does without
+    // Iterations of at most one round of a team (2 tasks per lane group and member) go to it; the staged kernel alone
+    // has one.  The plain evaluation relaxes whole rows of every vertex it reaches, which launches do as fast: it has
+    // teams only where all of its tasks are one round (256 vertices, all iterations in one launch: 181 -> 136 us; 4096,
+    // 32768 and 262144 vertices 244, 505 and 741 us without, 253, 520 and 775 with them).
+    const uint32_t round = (kBlock / 64) * T::G * 2;
+    const bool teams = staged && (!plain || max_tasks <= kTeamBlocks * round);
+    // a team lists tasks into a second buffer; a no-allocation call whose scratch holds one only does without
     const NoAlloc* na = noalloc_ctx();
-    const bool two = staged && (!na || na->used + 2 * max_tasks * 8 + 256 <= na->cap);
+    const bool two = teams && (!na || na->used + 2 * max_tasks * 8 + 256 <= na->cap);
     ra.tasks[0] = ws.buf<uint64_t>(Workspace::kTasks, (two ? 2 : 1) * max_tasks);
     ra.tasks[1] = two ? ra.tasks[0] + max_tasks : ra.tasks[0];
     ra.stamp = f.stamp;
@@ -1425,8 +1430,7 @@ void relax_phase(const Graph& g, const Window& W, const Window& PW, const uint32
         grid_for(((uint64_t)red.nU + red.TU / kRelaxChunk + T::G - 1) / T::G, kBlock / 64, EVQ_RELAX_BLOCKS);
     const uint32_t sblocks = grid_for((uint64_t)red.nU + red.TU / kRelaxChunk,
                                       (kBlock / 64) * T::G * (staged ? staged : 1), EVQ_RELAX_BLOCKS);
-    // iterations of at most one round of a team (2 tasks per lane group and member) go to it
-    const uint32_t team_tasks = two ? (kBlock / 64) * T::G * 2 : 0u;
+    const uint32_t team_tasks = two ? round : 0u;
     auto issue = [&](uint64_t, int p, bool first, unsigned long long* slot) {
         if (direct) {
             EVQ_LAUNCH("relax_compact", k_relax_compact<true>, cblocks, kCompactBlock, s, ra, p, first ? 1 : 0);
